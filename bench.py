@@ -74,7 +74,7 @@ def calibrate_copy(mib: int):
 
 
 def measured_traffic(workload_name: str, opts) -> float | None:
-    """HBM bytes per k_direct launch from the committed rocprofv3 counter passes, or None when the
+    """HBM bytes per direct-sum launch from the committed rocprofv3 counter passes, or None when the
     kernel source or the launch shape differs from the one the counters were taken on."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "traffic.json")
@@ -112,7 +112,7 @@ def issue_rates(P):
 
 def mix_ceiling(rates: dict, opts) -> dict | None:
     """Instruction-mix ceiling of the direct sum's lens loop: the loop's instructions per interaction
-    (counted in this build's gfx950 assembly, profiles/k_direct_isa_mix.json, valid while direct.hip
+    (counted in this build's gfx950 assembly, profiles/k_direct_isa_mix.json, valid while its source
     is unchanged) priced at the probe rates.  A reciprocal costs what it adds to a 13 : 1 mix of
     v_fmac_f32 and v_rcp_f32 (the lens loop's own proportion), 14 / R_mix - 13 / R_fmac."""
     import hashlib
@@ -270,7 +270,8 @@ def bench_batched(args, emit=True):
         "roofline": {"bound": "alu", "achieved": FLOP_PER_INTERACTION * inter / (batched_ms * 1e-3) / 1e12,
                      "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                      "frac": FLOP_PER_INTERACTION * inter / (batched_ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS,
-                     "traffic": None, "kernel": "k_batched"},
+                     "traffic": None,
+                     "kernel": "k_split_batched" if opts.block_cols in (0, 1) else "k_batched"},
     }
     if emit:
         print(json.dumps(out), flush=True)
@@ -649,7 +650,7 @@ def main():
         "rays_per_s": w.n_rays * args.steps / wall,
         "roofline": {"bound": "alu", "achieved": achieved_tf, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved_tf / PEAK_FP32_TFLOPS, "traffic": measured_traffic(w.name, opts),
-                     "kernel": "k_direct", "flop_per_interaction": FLOP_PER_INTERACTION,
+                     "kernel": "k_split" if opts.block_cols in (0, 1) else "k_direct", "flop_per_interaction": FLOP_PER_INTERACTION,
                      "kernel_ms": kernel_s * 1e3},
     }
     # the measured instruction-mix ceiling of the lens loop (issue-rate probes x counted mix)

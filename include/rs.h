@@ -149,7 +149,8 @@ typedef struct {
     int32_t fp32_run;        /* lenses per float32 run: 8, 16 or 32 (default 8 with one column,
                                 16 with several); one-column blocks add four runs in float32
                                 before each FP64 addition, several-column blocks add each run  */
-    int32_t map_window;      /* side of the LDS-privatised map window: 16, 32 or 64; -1 = off */
+    int32_t map_window;      /* side of the LDS-privatised map window: 16, 32 or 64; -1 = off   */
+                             /* (default: off with one-column blocks, 64 with several columns)  */
     double *ray_y;           /* optional device output, 2 doubles per ray of the window        */
     int32_t *ray_pix;        /* optional device output, pixel p2*n1+p1 per ray, -1 = lost      */
     uint32_t flags;          /* RS_FLAG_*                                                      */
@@ -157,7 +158,8 @@ typedef struct {
 
 /*
  * Workspace bytes rs_shoot needs for this job (8 partial maps, one per
- * accelerator complex die, plus alignment).  Returns 0 for an invalid job.
+ * accelerator complex die, 64 partial lost-ray counters, plus alignment).
+ * Returns 0 for an invalid job.
  */
 size_t rs_workspace_bytes(const rs_job *job, const rs_opts *opts);
 
@@ -175,7 +177,7 @@ int rs_shoot(const rs_job *job, void *workspace, size_t ws_bytes, void *stream, 
  * rs_shoot without a workspace, for callers that cannot allocate device memory: code being
  * captured into a HIP graph, tight serving loops, harnesses that forbid hipMalloc.  It computes
  * exactly what rs_shoot computes (same kernels, same counts and dumps), but its 8 partial maps
- * live in a fixed device array inside the library (32 MiB, held by every GPU the library runs
+ * live in a fixed device array inside the library (32 MiB and 8 KiB, held by every GPU the library runs
  * on until the process ends) instead of a caller workspace.  The map may have at most 2^20
  * bins (1024 x 1024); larger maps return RS_ERANGE before any HIP call (use rs_shoot).  The
  * first call on a device looks up the array's address there (hipGetSymbolAddress); no call

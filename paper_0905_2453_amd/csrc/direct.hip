@@ -16,66 +16,11 @@
 #include <algorithm>
 #include <mutex>
 
-#include "rs_internal.h"
+#include "direct_common.h"
 
 namespace rs {
 
 namespace {
-
-// Coordinate i of a grid axis at offset u in [0, 1) of its cell, FP64 then rounded to float32.
-__device__ __forceinline__ float ray_coord(double lo, double t, int64_t i, double u = 0.5)
-{
-    double v = ((double)i + u) * t;
-    double w = lo + v;
-    return (float)w;
-}
-
-// Half-open source pixel of y; returns p2 * n1 + p1, or -1 when the ray is lost.
-__device__ __forceinline__ int pixel_of(double y1, double y2, const DirectArgs &a, int &p1, int &p2)
-{
-    double f1 = floor((y1 - a.mlo1) * a.ms1);
-    double f2 = floor((y2 - a.mlo2) * a.ms2);
-    if (!(f1 >= 0.0 && f1 < (double)a.mn1 && f2 >= 0.0 && f2 < (double)a.mn2)) return -1;
-    p1 = (int)f1;
-    p2 = (int)f2;
-    return p2 * a.mn1 + p1;
-}
-
-// 1 / (1 + mean relative error of v_rcp_f32), the error measured over every float32 mantissa
-// in [1, 2) with weight 1/x.
-constexpr double kRcpBiasComp = 1.0 + 6.41e-9;
-
-// Ray and lens coordinates enter the lens loop scaled by 2^-4.  The scaling is exact, so every
-// rounding is that of the unscaled arithmetic; it keeps the product of four squared distances (four
-// rows sharing one reciprocal) in the float32 range for lenses up to about 1e6 from the rays.  The
-// sums come out 2^4 times the deflection and are scaled back with the bias compensation.
-constexpr float kLoopScale = 0.0625f;
-constexpr double kLoopBack = kRcpBiasComp * 0.0625;
-
-// One-column blocks add kQuadRuns consecutive float32 runs in float32 before the FP64 addition:
-// one float32 add per run instead of a conversion and an FP64 add, at an error between that of
-// single runs and of one run kQuadRuns times as long.
-constexpr int kQuadRuns = 4;
-
-// Lens i as the loop reads it: moved to the launch's time, coordinates scaled.
-__device__ __forceinline__ float4 loop_lens(const DirectArgs &a, int64_t i)
-{
-    float4 l = moved_lens(a.lenses[i], a.vel, i, a.time);
-    l.x *= kLoopScale;
-    l.y *= kLoopScale;
-    return l;
-}
-
-// Zero-mass padding of the last lens tile: at lens 0's position, so that its squared distances are
-// ordinary numbers (products stay finite and its terms are exactly zero); a ray exactly there takes
-// the per-ray recomputation below, as a ray on lens 0 does anyway.
-__device__ __forceinline__ float4 pad_lens(const DirectArgs &a)
-{
-    float4 l = loop_lens(a, 0);
-    l.z = 0.0f;
-    l.w = 0.0f;
-    return l;
-}
 
 template <int LT>
 struct TileSmem {
@@ -87,8 +32,8 @@ struct TileSmem {
 
 // Shoot one block of rays per lane with the whole workgroup: lane rays are the window-relative
 // columns c0 .. c0 + K1 - 1 and rows r0 .. r0 + K2 - 1 (r0 a multiple of 4); a ray counts only when
-// its column is below cmax and its row in [rmin, rmax).  `slot` selects the partial map the counts
-// go to.  Every thread of the workgroup must call it.
+// its column is below cmax and its row in [rmin, rmax).  `group` (a workgroup's number) selects the
+// partial map and the lost-ray counter.  Every thread of the workgroup must call it.
 //
 // Rays share reciprocals (simultaneous inversion).  With one column per lane, the four rows
 // r0 + 4p .. r0 + 4p + 3 share one: with q0 .. q3 their squared distances to a lens, g = 1 /
@@ -102,7 +47,7 @@ struct TileSmem {
 // gives g = 0: such a lens deflects by less than 1e-6 m and is dropped.
 template <int K1, int K2, int T, int LT, bool DUMP, bool JIT>
 __device__ __forceinline__ void shoot_rays(const DirectArgs &a, int64_t c0, int64_t r0, int64_t cmax, int64_t rmin,
-                                           int64_t rmax, uint32_t slot, TileSmem<LT> &sm)
+                                           int64_t rmax, uint32_t group, TileSmem<LT> &sm)
 {
     static_assert(K2 % 2 == 0, "rows pair up");
     constexpr int PER = LT / kThreads;
@@ -429,8 +374,7 @@ __device__ __forceinline__ void shoot_rays(const DirectArgs &a, int64_t c0, int6
         }
     }
 
-    // Window origin: per-axis median of 8 sample rays of the tile (robust to rays scattered
-    // far by a close lens).
+    // Window origin: per-axis median of 8 sample rays of the tile.
     const int W = a.window;
     int o1 = 0, o2 = 0;
     if (W > 0) {
@@ -444,41 +388,18 @@ __device__ __forceinline__ void shoot_rays(const DirectArgs &a, int64_t c0, int6
             s_cand[1][2 * wave + 1] = key[kb] >= 0 ? q2[kb] : INT_MIN;
         }
         __syncthreads();
-        int v1[2 * kWaves], v2[2 * kWaves], n = 0;
-#pragma unroll
-        for (int c = 0; c < 2 * kWaves; ++c) {
-            const int a1 = s_cand[0][c], a2 = s_cand[1][c];
-            if (a1 != INT_MIN) { v1[n] = a1; v2[n] = a2; ++n; }
-        }
-        if (n > 0) {
-            // insertion sorts of at most 8 values
-            for (int i = 1; i < n; ++i) {
-                int u = v1[i], w = v2[i], j = i - 1;
-                while (j >= 0 && v1[j] > u) { v1[j + 1] = v1[j]; --j; }
-                v1[j + 1] = u;
-                j = i - 1;
-                while (j >= 0 && v2[j] > w) { v2[j + 1] = v2[j]; --j; }
-                v2[j + 1] = w;
-            }
-            o1 = v1[n / 2] - W / 2;
-            o2 = v2[n / 2] - W / 2;
-        }
+        window_origin(s_cand[0], s_cand[1], lane, W, o1, o2);
     }
 
     // Binning: runs of equal keys among consecutive lanes are added once (wave aggregation),
     // into the LDS window when the pixel falls inside it, else into this die's partial map.
-    uint32_t *part = a.partial + (size_t)slot * (size_t)a.pstride;
+    uint32_t *part = a.partial + (size_t)(group & (kPartials - 1)) * (size_t)a.pstride;
     uint32_t lost_cnt = 0;
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const int kv = key[k];
-        const int prev = __shfl_up(kv, 1);
-        const bool head = (lane == 0) || (kv != prev);
-        const unsigned long long H = __ballot(head);
-        const unsigned long long above = lane == 63 ? 0ull : (H >> (lane + 1));
-        const int next = above ? lane + 1 + __builtin_ctzll(above) : 64;
-        const uint32_t cnt = (uint32_t)(next - lane);
-        if (head) {
+        uint32_t cnt;
+        if (run_head(kv, lane, cnt)) {
             if (kv >= 0) {
                 const int w1 = q1[k] - o1, w2 = q2[k] - o2;
                 if (W > 0 && (unsigned)w1 < (unsigned)W && (unsigned)w2 < (unsigned)W)
@@ -500,27 +421,27 @@ __device__ __forceinline__ void shoot_rays(const DirectArgs &a, int64_t c0, int6
             if (v) atomicAdd(&part[(int64_t)(o2 + b / W) * a.mn1 + (o1 + b % W)], v);
         }
     }
-    if (tid == 0 && s_lost) atomicAdd(a.lost, (unsigned long long)s_lost);
+    if (tid == 0 && s_lost) atomicAdd(lost_slot(a, group), (unsigned long long)s_lost);
 }
 
 // Ray tile `tile` of the window: (64 K1) columns x (4 K2) rows, lane l of wave w holding the
 // K1 x K2 block at columns c0 + K1 l, rows r0 + K2 w.
 template <int K1, int K2, int T, int LT, bool DUMP, bool JIT>
-__device__ __forceinline__ void shoot_tile(const DirectArgs &a, uint32_t tile, uint32_t slot, TileSmem<LT> &sm)
+__device__ __forceinline__ void shoot_tile(const DirectArgs &a, uint32_t tile, uint32_t group, TileSmem<LT> &sm)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int tx = (int)(tile % (uint32_t)a.tiles_x);
     const int ty = (int)(tile / (uint32_t)a.tiles_x);
     const int64_t c0 = (int64_t)tx * (64 * K1) + (int64_t)lane * K1;
     const int64_t r0 = (int64_t)ty * (kWaves * K2) + (int64_t)wave * K2;
-    shoot_rays<K1, K2, T, LT, DUMP, JIT>(a, c0, r0, a.wn1, a.rskip, a.wn2, slot, sm);
+    shoot_rays<K1, K2, T, LT, DUMP, JIT>(a, c0, r0, a.wn1, a.rskip, a.wn2, group, sm);
 }
 
 template <int K1, int K2, int T, int LT, bool DUMP, bool JIT>
 __global__ void __launch_bounds__(kThreads) k_direct(const DirectArgs a)
 {
     __shared__ TileSmem<LT> sm;
-    shoot_tile<K1, K2, T, LT, DUMP, JIT>(a, blockIdx.x, blockIdx.x & (kPartials - 1), sm);
+    shoot_tile<K1, K2, T, LT, DUMP, JIT>(a, blockIdx.x, blockIdx.x, sm);
 }
 
 // Persistent direct sum over the lane blocks of a list of culling cells (the cells a zoom
@@ -549,8 +470,7 @@ __global__ void __launch_bounds__(kThreads) k_direct_cells(const DirectArgs a, c
             cmax = min((mx + 1) * cb.c1, a.wn1);
             rmax = min((my + 1) * cb.c2 + a.rskip, a.wn2);
         }
-        shoot_rays<K1, K2, T, LT, false, JIT>(a, c0, r0, cmax, rmin, rmax, (blockIdx.x + it) & (kPartials - 1),
-                                             sm);
+        shoot_rays<K1, K2, T, LT, false, JIT>(a, c0, r0, cmax, rmin, rmax, blockIdx.x + it, sm);
         __syncthreads();
     }
 }
@@ -604,9 +524,18 @@ __global__ void __launch_bounds__(256) k_zero(uint4 *p, int64_t n4)
 
 // counts[b] += sum over the kPartials maps; partial maps are kPartials x pstride words with
 // pstride a multiple of 64, so every group of four bins is 16-byte aligned in the workspace.
+// The first wave also adds the kLostSlots lost-ray counters that follow the maps to *lost.
 __global__ void __launch_bounds__(256) k_reduce(const uint32_t *partial, int64_t bins, int64_t pstride,
-                                                 uint32_t *counts)
+                                                 uint32_t *counts, unsigned long long *lost)
 {
+    static_assert(kLostSlots == 64, "one counter per lane");
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        const auto *slots = reinterpret_cast<const unsigned long long *>(partial + (size_t)kPartials * pstride);
+        unsigned long long n = slots[(size_t)threadIdx.x * kLostStride];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+        if (threadIdx.x == 0 && n) atomicAdd(lost, n);
+    }
     const int64_t n4 = (bins + 3) / 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const bool vec = ((uintptr_t)counts & 15u) == 0;
@@ -740,7 +669,12 @@ bool ray_block_supported(int K1, int K2)
 hipError_t launch_direct(const DirectArgs &a, int K1, int K2, int T, int LT, int64_t n_tiles, hipStream_t s)
 {
     if (n_tiles <= 0) return hipSuccess;
-    if (K1 == 1 && K2 == 4) return launch_k<1, 4>(a, T, LT, n_tiles, s);
+    if (K1 == 1 && K2 == 4) {   // at most 64 lenses: the lens tile does not matter
+        if (T == 8) return launch_kt<1, 4, 8, 256>(a, n_tiles, s);
+        if (T == 16) return launch_kt<1, 4, 16, 256>(a, n_tiles, s);
+        if (T == 32) return launch_kt<1, 4, 32, 256>(a, n_tiles, s);
+        return hipErrorInvalidValue;
+    }
     if (K1 == 2 && K2 == 2) return launch_k<2, 2>(a, T, LT, n_tiles, s);
     if (K1 == 2 && K2 == 4) return launch_k<2, 4>(a, T, LT, n_tiles, s);
     if (K1 == 4 && K2 == 2) return launch_k<4, 2>(a, T, LT, n_tiles, s);
@@ -749,8 +683,8 @@ hipError_t launch_direct(const DirectArgs &a, int K1, int K2, int T, int LT, int
     return hipErrorInvalidValue;
 }
 
+// several-column blocks (the one-column ones are in split.hip)
 #define RS_BLOCK_SWITCH(FN, ...)                                              \
-    if (K1 == 1 && K2 == 4) return FN<1, 4>(__VA_ARGS__);                     \
     if (K1 == 2 && K2 == 2) return FN<2, 2>(__VA_ARGS__);                     \
     if (K1 == 2 && K2 == 4) return FN<2, 4>(__VA_ARGS__);                     \
     if (K1 == 4 && K2 == 2) return FN<4, 2>(__VA_ARGS__);                     \
@@ -804,13 +738,13 @@ hipError_t launch_zero(uint32_t *p, int64_t n_words, hipStream_t s)
 }
 
 hipError_t launch_reduce(const uint32_t *partial, int64_t bins, int64_t pstride, uint32_t *counts,
-                         hipStream_t s)
+                         unsigned long long *lost, hipStream_t s)
 {
     const int64_t n4 = (bins + 3) / 4;
     if (n4 <= 0) return hipSuccess;
     int64_t blocks = (n4 + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_reduce, dim3((unsigned)blocks), dim3(256), 0, s, partial, bins, pstride, counts);
+    hipLaunchKernelGGL(k_reduce, dim3((unsigned)blocks), dim3(256), 0, s, partial, bins, pstride, counts, lost);
     return hipGetLastError();
 }
 

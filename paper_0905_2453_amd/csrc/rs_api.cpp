@@ -39,10 +39,14 @@ bool is_fin(double v) { return std::isfinite(v); }
 constexpr double kMaxCoord = 1.0e12;  // far below the position of the zero-mass padding lenses
 
 // Resolved tuning of one direct-sum launch.  T = 0 selects the float32 run length of the block
-// shape: 8 lenses with one column per lane (four rows share a reciprocal), 16 with several (pairs).
+// shape: 8 lenses with one column per lane (four rows share a reciprocal), 16 with several (pairs).  W = -1
+// selects its map window: none with one column (its lane runs already merge most rays of a pixel: 1000^2 rays,
+// 400 lenses 73.7 us, with a 16 x 16 window 75.8, with a 64 x 64 one 80.7; 4096 x 2048 rays, 16 lenses, 20 x 20
+// pixels: 54.9, 59.8, 64.9), 64 x 64 with several.
 struct Tune {
-    int K1 = 1, K2 = 4, T = 0, LT = 256, W = 64;
+    int K1 = 1, K2 = 4, T = 0, LT = 256, W = -1;
     int run() const { return T ? T : (K1 == 1 ? 8 : 16); }
+    int window() const { return W >= 0 ? W : (K1 == 1 ? 0 : 64); }
 };
 
 int resolve_opts(const rs_opts *o, Tune &t)
@@ -123,6 +127,16 @@ int64_t partial_stride(const rs_job *j)
     const int64_t bins = (int64_t)j->map.n[0] * j->map.n[1];
     return (bins + 63) / 64 * 64;
 }
+// 32-bit words of a launch's partial maps and the lost-ray counters after them
+int64_t partial_words(const rs_job *j) { return rs::kPartials * partial_stride(j) + rs::kLostWords; }
+
+// Counts of the launch go to the partial maps at `part`, its lost rays to the counters after them.
+void use_partials(rs::DirectArgs &a, uint32_t *part)
+{
+    a.partial = part;
+    a.lost = reinterpret_cast<unsigned long long *>(part + rs::kPartials * a.pstride);
+    a.lost_mask = rs::kLostSlots - 1;
+}
 
 // Device-side description of one job for a K1 x K2 ray block; counts go to `partial`.
 rs::DirectArgs make_args(const rs_job *job, const Tune &t, uint32_t *partial, int64_t pstride,
@@ -149,7 +163,7 @@ rs::DirectArgs make_args(const rs_job *job, const Tune &t, uint32_t *partial, in
     a.ms2 = (double)job->map.n[1] / (job->map.hi[1] - job->map.lo[1]);
     a.mn1 = job->map.n[0];
     a.mn2 = job->map.n[1];
-    a.window = t.W;
+    a.window = t.window();
     a.partial = partial;
     a.pstride = pstride;
     a.lost = reinterpret_cast<unsigned long long *>(job->n_lost);
@@ -163,6 +177,8 @@ rs::DirectArgs make_args(const rs_job *job, const Tune &t, uint32_t *partial, in
     a.jkey2 = rs::jitter_key(g.jitter_seed, 1);
     a.vel = reinterpret_cast<const float2 *>(job->velocities);
     a.time = job->time;
+    a.n_blocks = (uint32_t)(((g.win_n[0] + 63) / 64) * ((a.wn2 + 3) / 4));
+    a.per_item = 1;
     return a;
 }
 
@@ -210,10 +226,11 @@ struct GraphKey {
     void *ws;
     int device, K1, K2, T, LT, W, grid, n_jobs;
     uint32_t n_items;
+    int waves;
     bool operator<(const GraphKey &o) const
     {
-        return std::tie(ws, device, K1, K2, T, LT, W, grid, n_jobs, n_items) <
-               std::tie(o.ws, o.device, o.K1, o.K2, o.T, o.LT, o.W, o.grid, o.n_jobs, o.n_items);
+        return std::tie(ws, device, K1, K2, T, LT, W, grid, n_jobs, n_items, waves) <
+               std::tie(o.ws, o.device, o.K1, o.K2, o.T, o.LT, o.W, o.grid, o.n_jobs, o.n_items, o.waves);
     }
 };
 std::map<GraphKey, hipGraphExec_t> g_graphs;
@@ -224,6 +241,7 @@ struct PreparedBatch {
     uint64_t interactions = 0;  // ray-lens interactions of the items taken
     int grid = 0;
     int device = 0;
+    int waves = 0;              // waves of a workgroup that split the lenses (one-column blocks)
 };
 
 // Validate, order by decreasing work per tile, upload the job table into the workspace and fill
@@ -258,7 +276,13 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     std::vector<uint8_t> host(table_bytes + start_bytes);
     auto *args = reinterpret_cast<rs::DirectArgs *>(host.data());
     auto *start = reinterpret_cast<uint32_t *>(host.data() + table_bytes);
-    uint64_t items = 0, taken = 0, inter = 0;
+    // Work items: a tile of rays, or of one-column blocks as many as make up about 2048 lenses' work (an item
+    // taken from the counter costs about 12 ns), and at least so many that their number stays below that of
+    // the tiles where it could pass 2^31.
+    uint64_t items = 0, taken = 0, inter = 0, tiles = 0;
+    for (int32_t k = 0; k < n_jobs; ++k) tiles += (uint64_t)tile_count(&jobs[k], t);
+    if (tiles >= (uint64_t(1) << 31)) return fail(RS_ERANGE, "more than 2^31 ray tiles in one batch");
+    const int64_t least = tiles >= (uint64_t(1) << 29) ? rs::kWaves : 1;
     const uint64_t rays_per_tile = 64ull * (uint64_t)t.K1 * (uint64_t)rs::kWaves * (uint64_t)t.K2;
     start[0] = 0;
     for (int32_t k = 0; k < n_jobs; ++k) {
@@ -272,13 +296,18 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
         } else {
             args[k] = make_args(job, t, counts, 0, nullptr);
         }
-        const int64_t nt = tile_count(job, t);
+        int64_t nt = tile_count(job, t);
+        uint64_t rays_per_item = rays_per_tile;
+        if (t.K1 == 1) {
+            const int64_t q = std::max(least, std::min<int64_t>(16, 2048 / std::max<int64_t>(job->n_lens, 1)));
+            args[k].per_item = (uint32_t)q;
+            nt = ((int64_t)args[k].n_blocks + q - 1) / q;
+            rays_per_item = 256ull * (uint64_t)q;
+        }
         items += (uint64_t)nt;
-        if (items >= (uint64_t(1) << 31)) return fail(RS_ERANGE, "more than 2^31 ray tiles in one batch");
         start[k + 1] = (uint32_t)items;
-        for (int64_t i = 0; i < nt; ++i) {
-            if (item_budget && inter >= item_budget) break;
-            inter += rays_per_tile * (uint64_t)job->n_lens;
+        for (int64_t i = 0; item_budget && i < nt && inter < item_budget; ++i) {
+            inter += rays_per_item * (uint64_t)job->n_lens;
             ++taken;
         }
     }
@@ -288,7 +317,9 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return dev_fail(e, "device query");
-    const int occ = rs::batched_occupancy(t.K1, t.K2, t.run(), t.LT);
+    if (t.K1 == 1) pb.waves = rs::split_batched_waves(n_jobs > 0 ? jobs[order[0]].n_lens : 0);
+    const int occ = t.K1 == 1 ? rs::split_batched_occupancy(t.run(), t.LT, pb.waves)
+                              : rs::batched_occupancy(t.K1, t.K2, t.run(), t.LT);
     if (occ <= 0) return fail(RS_EINTERNAL, "no occupancy for the batched kernel");
 
     {
@@ -321,14 +352,17 @@ int run_batch(const PreparedBatch &pb, const Tune &t, void *workspace, hipStream
     if (pb.args.n_items == 0) return RS_OK;
     auto enqueue = [&]() -> hipError_t {
         hipError_t e = rs::launch_fill_u32(pb.args.queue, 1, 0u, s);
-        if (e == hipSuccess) e = rs::launch_batched(pb.args, t.K1, t.K2, t.run(), t.LT, pb.grid, s);
+        if (e == hipSuccess)
+            e = t.K1 == 1 ? rs::launch_split_batched(pb.args, t.run(), t.LT, pb.waves, pb.grid, s)
+                          : rs::launch_batched(pb.args, t.K1, t.K2, t.run(), t.LT, pb.grid, s);
         return e;
     };
     if (!use_graph || s == nullptr) {
         const hipError_t e = enqueue();
         return e == hipSuccess ? RS_OK : dev_fail(e, "batched launch");
     }
-    const GraphKey key{workspace, pb.device, t.K1, t.K2, t.run(), t.LT, t.W, pb.grid, pb.args.n_jobs, pb.args.n_items};
+    const GraphKey key{workspace, pb.device, t.K1, t.K2, t.run(), t.LT, t.W, pb.grid, pb.args.n_jobs, pb.args.n_items,
+                       pb.waves};
     hipGraphExec_t exec = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_mu);
@@ -512,12 +546,18 @@ int shoot_with_partials(const rs_job *job, const Tune &t, uint32_t *part, hipStr
 {
     const int64_t pstride = partial_stride(job);
     const int64_t bins = (int64_t)job->map.n[0] * job->map.n[1];
-    const rs::DirectArgs a = make_args(job, t, part, pstride, opts);
-    hipError_t e = rs::launch_zero(part, rs::kPartials * pstride, s);
+    rs::DirectArgs a = make_args(job, t, part, pstride, opts);
+    use_partials(a, part);
+    hipError_t e = rs::launch_zero(part, partial_words(job), s);
     if (e != hipSuccess) return dev_fail(e, "zero partial maps");
-    e = rs::launch_direct(a, t.K1, t.K2, t.run(), t.LT, tile_count(job, t), s);
+    // One-column blocks split the lenses over waves; with one or two groups of lenses most waves would have
+    // none, and on large windows k_direct, whose workgroup takes four times the rays, is the faster one
+    // (4096 x 2048 rays, 64 lenses: 108 us against 134, 101 lenses 180 against 163; 640 x 512 rays, 64
+    // lenses: 16.8 against 13.5).
+    if (t.K1 == 1 && (job->n_lens > 64 || a.n_blocks < 2048)) e = rs::launch_split(a, t.run(), t.LT, s);
+    else e = rs::launch_direct(a, t.K1, t.K2, t.run(), t.LT, tile_count(job, t), s);
     if (e != hipSuccess) return dev_fail(e, "direct-sum launch");
-    e = rs::launch_reduce(part, bins, pstride, job->counts, s);
+    e = rs::launch_reduce(part, bins, pstride, job->counts, reinterpret_cast<unsigned long long *>(job->n_lost), s);
     if (e != hipSuccess) return dev_fail(e, "map reduce launch");
     return RS_OK;
 }
@@ -565,7 +605,7 @@ size_t rs_workspace_bytes(const rs_job *job, const rs_opts *opts)
 {
     Tune t;
     if (validate_job(job) != RS_OK || resolve_opts(opts, t) != RS_OK) return 0;
-    return (size_t)(rs::kPartials * partial_stride(job)) * sizeof(uint32_t) + 256;
+    return (size_t)partial_words(job) * sizeof(uint32_t) + 256;
 }
 
 int rs_shoot(const rs_job *job, void *workspace, size_t ws_bytes, void *stream, const rs_opts *opts)
@@ -691,7 +731,7 @@ int zoom_layout(const rs_job *job, const rs_zoom *z, const Tune &t, ZoomLayout &
         off += align256((size_t)(L.lnx[l] * L.lny[l]) * sizeof(uint32_t));
     }
     L.part_off = off;
-    off += (size_t)(rs::kPartials * partial_stride(job)) * sizeof(uint32_t);
+    off += (size_t)partial_words(job) * sizeof(uint32_t);
     L.total = off + 256;
     return RS_OK;
 }
@@ -983,9 +1023,9 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     uint32_t *stats = reinterpret_cast<uint32_t *>(base);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // statistics: [0] kept cells (the list length), [1] cells, [2] lane blocks per cell,
-    // [3] rays per lane block, [4 + l] kept cells of the coarser level l < levels - 1
+    // [3] rays per lane block, [4 + l] kept cells of the coarser level l < levels - 1, [8] work counter
     static_assert(rs::kZoomLevels <= 5, "the statistics block holds four coarser levels");
-    hipError_t e = rs::launch_fill_u32(stats, 8, 0u, s);
+    hipError_t e = rs::launch_fill_u32(stats, 9, 0u, s);
     if (e == hipSuccess) e = rs::launch_fill_u32(stats + 1, 1, (uint32_t)L.cells, s);
     if (e == hipSuccess) e = rs::launch_fill_u32(stats + 2, 1, (uint32_t)L.S, s);
     if (e == hipSuccess) e = rs::launch_fill_u32(stats + 3, 1, (uint32_t)(t.K1 * t.K2), s);
@@ -996,7 +1036,8 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     uint32_t *part = reinterpret_cast<uint32_t *>(base + L.part_off);
     const int64_t pstride = partial_stride(job);
     const int64_t bins = (int64_t)job->map.n[0] * job->map.n[1];
-    const rs::DirectArgs a = make_args(job, t, part, pstride, opts);
+    rs::DirectArgs a = make_args(job, t, part, pstride, opts);
+    use_partials(a, part);
 
     rs::ZoomArgs z{};
     z.lenses = reinterpret_cast<const float4 *>(job->lenses);
@@ -1043,6 +1084,7 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     rs::CellBlocks cb{};
     cb.list = z.list;
     cb.count = stats;
+    cb.queue = stats + 8;
     cb.c1 = L.c1;
     cb.c2 = L.c2;
     cb.ncx = L.ncx;
@@ -1050,13 +1092,14 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     cb.S = L.S;
     const int64_t max_groups = (L.cells * L.S + rs::kThreads - 1) / rs::kThreads;
 
-    e = rs::launch_zero(part, rs::kPartials * pstride, s);
+    e = rs::launch_zero(part, partial_words(job), s);
     if (e != hipSuccess) return dev_fail(e, "zero partial maps");
     e = rs::launch_zoom_mark(z, s);
     if (e != hipSuccess) return dev_fail(e, "zoom culling launch");
-    e = rs::launch_direct_cells(a, t.K1, t.K2, t.run(), t.LT, cb, max_groups, s);
+    if (t.K1 == 1) e = rs::launch_split_cells(a, t.run(), t.LT, cb, L.cells * L.S, s);
+    else e = rs::launch_direct_cells(a, t.K1, t.K2, t.run(), t.LT, cb, max_groups, s);
     if (e != hipSuccess) return dev_fail(e, "zoom direct-sum launch");
-    e = rs::launch_reduce(part, bins, pstride, job->counts, s);
+    e = rs::launch_reduce(part, bins, pstride, job->counts, reinterpret_cast<unsigned long long *>(job->n_lost), s);
     if (e != hipSuccess) return dev_fail(e, "map reduce launch");
     return RS_OK;
 }

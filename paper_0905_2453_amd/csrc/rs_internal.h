@@ -14,8 +14,11 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kMaxWindow = 64;          // LDS map window side (bins)
 constexpr int kPartials = 8;            // partial maps, one per accelerator complex die
 constexpr float kPadCoord = 1.0e18f;    // position of the zero-mass lenses padding a tile
+constexpr int kLostSlots = 64;          // lost-ray counters of a launch, kLostStride 64-bit words apart
+constexpr int kLostStride = 16;
+constexpr int64_t kLostWords = 2 * kLostSlots * kLostStride;           // 8 KiB after the partial maps
 constexpr int kNoAllocBins = 1 << 20;   // largest map rs_shoot_noalloc takes (1024 x 1024 bins)
-constexpr int64_t kNoAllocWords = (int64_t)kPartials * kNoAllocBins;   // its fixed scratch: 32 MiB
+constexpr int64_t kNoAllocWords = (int64_t)kPartials * kNoAllocBins + kLostWords;   // its fixed scratch
 
 // Everything one direct-sum launch needs, already reduced to FP64 constants on the host.
 struct DirectArgs {
@@ -37,7 +40,8 @@ struct DirectArgs {
     int32_t window;         // LDS window side, 0 = all bins go to global atomics
     uint32_t *partial;      // kPartials maps of mn1*mn2 bins, pstride words apart
     int64_t pstride;        // words between partial maps (multiple of 64)
-    unsigned long long *lost;
+    unsigned long long *lost;   // lost_mask + 1 counters, kLostStride words apart
+    uint32_t lost_mask;     // 0: the job's own counter, else kLostSlots - 1
     double *ray_y;          // optional per-ray dump (window-relative index)
     int32_t *ray_pix;
     int64_t gn1;            // full grid width (ray index for the jitter hash)
@@ -45,6 +49,8 @@ struct DirectArgs {
     int32_t jitter;
     const float2 *vel;      // lens velocities or null (static field)
     double time;            // lens i sits at x_i + v_i time
+    uint32_t n_blocks;      // split kernels: 64-column x 4-row blocks of the window ...
+    uint32_t per_item;      // ... and consecutive blocks per work item of a batch
 };
 
 // Lens record i of a field that may move: positions advanced in FP64, rounded to float32.
@@ -185,6 +191,7 @@ hipError_t launch_advance(const float4 *in, const float2 *vel, int64_t n, double
 struct CellBlocks {
     const uint32_t *list;
     const uint32_t *count;
+    uint32_t *queue;        // work counter of the split kernel, zeroed before each launch
     int64_t c1, c2, ncx;    // culling cell size (window columns, rows) and cells per row
     int64_t sx, S;          // lane blocks per cell row, lane blocks per cell
 };
@@ -218,6 +225,13 @@ bool ray_block_supported(int K1, int K2);
 // Launch the direct-sum kernel for a K1 x K2 ray block per lane, T-lens float32 runs and LT-lens
 // LDS tiles.
 hipError_t launch_direct(const DirectArgs &a, int K1, int K2, int T, int LT, int64_t n_tiles, hipStream_t s);
+// One-column blocks, lenses split over a workgroup's waves: a window, the lane blocks of a cell list, a batch
+// (WV waves a workgroup, split_batched_waves of the batch's largest lens count).
+hipError_t launch_split(const DirectArgs &a, int T, int LT, hipStream_t s);
+hipError_t launch_split_cells(const DirectArgs &a, int T, int LT, const CellBlocks &cb, int64_t blocks, hipStream_t s);
+int split_batched_waves(int64_t most_lenses);
+hipError_t launch_split_batched(const BatchArgs &b, int T, int LT, int WV, int grid, hipStream_t s);
+int split_batched_occupancy(int T, int LT, int WV);
 // Launch the persistent batched kernel on `grid` workgroups.
 hipError_t launch_batched(const BatchArgs &b, int K1, int K2, int T, int LT, int grid, hipStream_t s);
 // Resident workgroups per compute unit of the batched kernel (0 on error).
@@ -226,9 +240,9 @@ int batched_occupancy(int K1, int K2, int T, int LT);
 hipError_t launch_fill_u32(uint32_t *p, int n, uint32_t v, hipStream_t s);
 // Zero the partial maps (fill kernel; graph-capture safe).
 hipError_t launch_zero(uint32_t *p, int64_t n_words, hipStream_t s);
-// counts[b] += sum_s partial[s * pstride + b] for b < bins.
+// counts[b] += sum_s partial[s * pstride + b] for b < bins; *lost += the lost-ray counters after the maps.
 hipError_t launch_reduce(const uint32_t *partial, int64_t bins, int64_t pstride, uint32_t *counts,
-                         hipStream_t s);
+                         unsigned long long *lost, hipStream_t s);
 // mu[b] = counts[b] / n_av for b < bins (FP64).
 hipError_t launch_magnification(const uint32_t *counts, int64_t bins, double n_av, double *mu, hipStream_t s);
 // Issue-rate probes (rs_probe.h): lane instructions per loop iteration of probe `op`, and one launch.

@@ -1,0 +1,466 @@
+// Direct inverse ray-shooting with the lenses split over the waves of a workgroup: the one-column ray
+// blocks of rs_shoot, rs_shoot_batched and rs_shoot_zoom.
+//
+// Method: Thompson, Fluke, Barnes & Barsdell (2009), section 1 eqs. 1, 2, 4; section 2 eq. 5 (the sum
+// over the lenses as partial sums over subsets); section 3.2 eq. 6.
+//
+// Work decomposition.  The WV waves of a workgroup share 64 blocks of four rays: lane l holds column
+// c0 + l, rows r0 .. r0 + 3 (or its own block out of a list of culling cells).  Wave w sums the groups of
+// T kQuadRuns lenses w, w + WV, w + 2 WV, ... of the field; every group is summed operation by operation as
+// k_direct sums it, and the waves' FP64 sums meet in LDS in wave order.  FP64 addition of the groups'
+// float32 sums is exact while they stay within 2^29 of each other (24-bit numbers in a 53-bit sum), so
+// the order does not show in a ray's position, and the maps are those of k_direct.
+#include <algorithm>
+
+#include "direct_common.h"
+
+namespace rs {
+
+namespace {
+
+// Where the four rays of a lane lie: on rows that all lanes share, on rows of the lane's own, or each at
+// a random point of its cell.
+enum RayMode { kSharedRows = 0, kOwnRows = 1, kJitter = 2 };
+
+// B lenses are staged by a wave at a time (private to it: the lens loop has no barrier).
+template <int B, int WV>
+struct SplitSmem {
+    union {
+        struct {
+            float4 dy[WV][B];    // kSharedRows: x2 - x2_i of the four rows; else the lens record
+            float2 xm[WV][B];    // kSharedRows: x1_i and the mass
+        } st;
+        double2 sum[WV][4][64];  // the waves' sums, after the lens loop
+        uint32_t win[kMaxWindow * kMaxWindow];
+    };
+    uint32_t bad[64];
+    int cand[2][8];
+    uint32_t lost;
+};
+
+// A wave's LDS accesses are performed in order; this keeps the compiler to the order as well.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One float32 run of T staged lenses for the lane's four rays: the arithmetic of shoot_rays with four
+// rows per reciprocal.
+template <int T, RayMode MODE, int B, int WV>
+__device__ __forceinline__ void quad_run(const SplitSmem<B, WV> &sm, int wave, int at, const float *x1, const float *x2,
+                                         float *s1, float *s2)
+{
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+        float dx[4], dx2[4], dy[4], q[4], m;
+        const float4 l = sm.st.dy[wave][at + j];
+        if constexpr (MODE == kSharedRows) {
+            const float2 xm = sm.st.xm[wave][at + j];
+            m = xm.y;
+            dx[0] = x1[0] - xm.x;
+            dy[0] = l.x;
+            dy[1] = l.y;
+            dy[2] = l.z;
+            dy[3] = l.w;
+        } else {
+            m = l.z;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dy[e] = x2[e] - l.y;
+#pragma unroll
+            for (int e = 0; e < (MODE == kJitter ? 4 : 1); ++e) dx[e] = x1[e] - l.x;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (MODE != kJitter && e > 0) dx[e] = dx[0];
+            dx2[e] = MODE != kJitter && e > 0 ? dx2[0] : dx[e] * dx[e];
+            q[e] = fmaf(dy[e], dy[e], dx2[e]);
+        }
+        const float p01 = q[0] * q[1], p23 = q[2] * q[3];
+        const float g = m * __builtin_amdgcn_rcpf(p01 * p23);
+        const float g01 = g * p23, g23 = g * p01;
+        const float d[4] = {g01 * q[1], g01 * q[0], g23 * q[3], g23 * q[2]};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            s1[e] = j == 0 ? d[e] * dx[e] : fmaf(d[e], dx[e], s1[e]);
+            s2[e] = j == 0 ? d[e] * dy[e] : fmaf(d[e], dy[e], s2[e]);
+        }
+    }
+}
+
+// Shoot the workgroup's 64 blocks of four rays.  The lane's block starts at window column c0 and row r0
+// (a multiple of 4); a ray counts when its column is below cmax and its row in [rmin, rmax).  `group` (a
+// workgroup's number) selects the partial map and the lost-ray counter.  Every thread of the workgroup
+// must call it, lane l of every wave with the same block.
+//
+// Bound: issue of the lens loop.  The rows of kSharedRows belong to all lanes alike, so the lane that stages
+// a lens takes x2 - x2_i of the four rows once and the loop reads the four back as one broadcast
+// ds_read_b128: 24 FP32 instructions and a reciprocal per lens and four rays, where every lane subtracting
+// them itself takes 28.  1e5 lenses, 4096^2 rays: 192.4 ms (8.72e12 interactions/s), k_direct 206.3 ms on the
+// same box; 512^2 rays, which fill a quarter of the chip's wave slots as blocks of 1024: 3.5 ms, k_direct 8.0.
+template <int T, int B, int WV, RayMode MODE, bool DUMP>
+__device__ __forceinline__ void shoot_split(const DirectArgs &a, uint32_t c0, uint32_t r0, int64_t cmax, int64_t rmin,
+                                            int64_t rmax, uint32_t group, SplitSmem<B, WV> &sm)
+{
+    constexpr int GS = T * kQuadRuns, NG = B / GS, PL = B / 64, NX = MODE == kJitter ? 4 : 1;
+    static_assert(B % GS == 0 && B % 64 == 0 && (GS & (GS - 1)) == 0 && WV >= 4, "staging shape");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    float x1[NX], x2[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int64_t g1 = a.wlo1 + c0, g2 = a.wlo2 + r0 + e, r = g2 * a.gn1 + g1;
+        if (e < NX) x1[e] = ray_coord(a.glo1, a.gt1, g1, MODE == kJitter ? jitter_u(a.jkey1, r) : 0.5) * kLoopScale;
+        x2[e] = ray_coord(a.glo2, a.gt2, g2, MODE == kJitter ? jitter_u(a.jkey2, r) : 0.5) * kLoopScale;
+        if (MODE == kSharedRows) x2[e] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x2[e])));
+    }
+
+    // the wave's k-th group is group k WV + wave of the field; staged lens `at` belongs to its group
+    // gb + at / GS
+    auto lens_index = [&](int64_t gb, int at) -> int64_t {
+        return ((gb + at / GS) * WV + wave) * GS + (at & (GS - 1));
+    };
+    const int64_t n_groups = (a.n_lens + GS - 1) / GS;
+    const int64_t my_groups = n_groups > wave ? (n_groups - wave + WV - 1) / WV : 0;
+    float4 reg[PL];
+    auto fetch = [&](int64_t gb) {
+#pragma unroll
+        for (int p = 0; p < PL; ++p) {
+            const int64_t i = lens_index(gb, p * 64 + lane);
+            const bool in = i < a.n_lens;
+            reg[p] = moved_lens(a.lenses[in ? i : 0], a.vel, in ? i : 0, a.time);
+            if (!in) reg[p].z = 0.0f;            // padding as pad_lens: lens 0's position, no mass
+        }
+    };
+    double A1[4] = {}, A2[4] = {};
+    if (my_groups > 0) fetch(0);
+    for (int64_t gb = 0; gb < my_groups; gb += NG) {
+#pragma unroll
+        for (int p = 0; p < PL; ++p) {
+            float4 l = reg[p];
+            l.x *= kLoopScale;
+            l.y *= kLoopScale;
+            if constexpr (MODE == kSharedRows) {
+                sm.st.dy[wave][p * 64 + lane] = make_float4(x2[0] - l.y, x2[1] - l.y, x2[2] - l.y, x2[3] - l.y);
+                sm.st.xm[wave][p * 64 + lane] = make_float2(l.x, l.z);
+            } else {
+                sm.st.dy[wave][p * 64 + lane] = l;
+            }
+        }
+        wave_fence();
+        if (gb + NG < my_groups) fetch(gb + NG);
+        const int ng = (int)min((int64_t)NG, my_groups - gb);
+        for (int k = 0; k < ng; ++k) {
+            const int64_t left = a.n_lens - lens_index(gb, k * GS);
+            float m1[4], m2[4];
+            if (left >= GS) {
+#pragma unroll
+                for (int h = 0; h < kQuadRuns; ++h) {
+                    float s1[4], s2[4];
+                    quad_run<T, MODE>(sm, wave, k * GS + h * T, x1, x2, s1, s2);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        m1[e] = h == 0 ? s1[e] : m1[e] + s1[e];
+                        m2[e] = h == 0 ? s2[e] : m2[e] + s2[e];
+                    }
+                }
+            } else {
+                // the field's last group: only the runs that hold a lens (padding alone adds exact zeros)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m1[e] = m2[e] = 0.0f;
+                const int runs = (int)((left + T - 1) / T);
+                for (int h = 0; h < runs; ++h) {
+                    float s1[4], s2[4];
+                    quad_run<T, MODE>(sm, wave, k * GS + h * T, x1, x2, s1, s2);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        m1[e] += s1[e];
+                        m2[e] += s2[e];
+                    }
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                A1[e] += (double)m1[e];
+                A2[e] += (double)m2[e];
+            }
+        }
+        wave_fence();
+    }
+
+    // From here on thread (w, l), w < 4, owns the ray of row r0 + w of block l; further waves only help with
+    // the window.
+    const bool owner = wave < 4;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sm.sum[wave][e][lane] = make_double2(A1[e], A2[e]);
+    if (tid < 64) sm.bad[tid] = 0u;
+    if (tid == 0) sm.lost = 0u;
+    __syncthreads();
+    double B1 = 0.0, B2 = 0.0;
+    if (owner) {
+#pragma unroll
+        for (int w = 0; w < WV; ++w) {
+            const double2 v = sm.sum[w][wave][lane];
+            B1 += v.x;
+            B2 += v.y;
+        }
+        if (!__builtin_isfinite(B1 + B2)) sm.bad[lane] = 1u;
+    }
+    const int64_t row = (int64_t)r0 + (owner ? wave : 0);
+    const int64_t g1 = a.wlo1 + c0, g2 = a.wlo2 + row, rg = g2 * a.gn1 + g1;
+    const float X1 = ray_coord(a.glo1, a.gt1, g1, MODE == kJitter ? jitter_u(a.jkey1, rg) : 0.5) * kLoopScale;
+    const float X2 = ray_coord(a.glo2, a.gt2, g2, MODE == kJitter ? jitter_u(a.jkey2, rg) : 0.5) * kLoopScale;
+    __syncthreads();
+    if (owner && sm.bad[lane]) {
+        // see shoot_rays: a block with a non-finite sum is redone with one reciprocal per ray, in the same
+        // runs and groups
+        B1 = B2 = 0.0;
+        float m1 = 0.0f, m2 = 0.0f;
+        for (int64_t r = 0; r < a.n_lens; r += T) {
+            float s1 = 0.0f, s2 = 0.0f;
+            const int64_t e = min(r + (int64_t)T, a.n_lens);
+            for (int64_t li = r; li < e; ++li) {
+                const float4 l = loop_lens(a, li);
+                const float dx = X1 - l.x, dy = X2 - l.y;
+                const float d = l.z * __builtin_amdgcn_rcpf(fmaf(dy, dy, dx * dx));
+                s1 = fmaf(d, dx, s1);
+                s2 = fmaf(d, dy, s2);
+            }
+            const bool first = (r / T) % kQuadRuns == 0, last = (r / T) % kQuadRuns == kQuadRuns - 1 || e == a.n_lens;
+            m1 = first ? s1 : m1 + s1;
+            m2 = first ? s2 : m2 + s2;
+            if (last) {
+                B1 += (double)m1;
+                B2 += (double)m2;
+            }
+        }
+    }
+    B1 *= kLoopBack;
+    B2 *= kLoopBack;
+
+    // Lens equation (eq. 6), source pixel and binning as in shoot_rays, one ray per thread.
+    const bool ok = owner && c0 < cmax && row >= rmin && row < rmax;
+    const double y1 = a.lam1 * ((double)X1 * 16.0) - B1;
+    const double y2 = a.lam2 * ((double)X2 * 16.0) - B2;
+    int p1 = 0, p2 = 0;
+    const int kv = pixel_of(y1, y2, a, p1, p2);
+    const int key = ok ? kv : -2;
+    if (DUMP && ok) {
+        const int64_t ri = (row - a.rskip) * a.wn1 + c0;
+        a.ray_y[2 * ri] = y1;
+        a.ray_y[2 * ri + 1] = y2;
+        a.ray_pix[ri] = kv;
+    }
+    const int W = a.window;
+    int o1 = 0, o2 = 0;
+    if (W > 0) {
+        for (int b = tid; b < W * W; b += 64 * WV) sm.win[b] = 0u;
+        if (owner && (lane == 16 || lane == 48)) {
+            sm.cand[0][2 * wave + (lane >> 5)] = key >= 0 ? p1 : INT_MIN;
+            sm.cand[1][2 * wave + (lane >> 5)] = key >= 0 ? p2 : INT_MIN;
+        }
+        __syncthreads();
+        window_origin(sm.cand[0], sm.cand[1], lane, W, o1, o2);
+    }
+    uint32_t *part = a.partial + (size_t)(group & (kPartials - 1)) * (size_t)a.pstride;
+    if (owner) {
+        uint32_t cnt;
+        if (run_head(key, lane, cnt)) {
+            if (key >= 0) {
+                const int w1 = p1 - o1, w2 = p2 - o2;
+                if (W > 0 && (unsigned)w1 < (unsigned)W && (unsigned)w2 < (unsigned)W)
+                    atomicAdd(&sm.win[w2 * W + w1], cnt);
+                else
+                    atomicAdd(&part[key], cnt);
+            } else if (key == -1) {
+                atomicAdd(&sm.lost, cnt);
+            }
+        }
+    }
+    __syncthreads();
+    if (W > 0) {
+        for (int b = tid; b < W * W; b += 64 * WV) {
+            const uint32_t v = sm.win[b];
+            if (v) atomicAdd(&part[(int64_t)(o2 + b / W) * a.mn1 + (o1 + b % W)], v);
+        }
+    }
+    if (tid == 0 && sm.lost) atomicAdd(lost_slot(a, group), (unsigned long long)sm.lost);
+}
+
+// Block `tile` of the window: 64 columns x 4 rows.
+template <int T, int B, int WV, bool DUMP, bool JIT>
+__device__ __forceinline__ void split_tile(const DirectArgs &a, uint32_t tile, uint32_t group, SplitSmem<B, WV> &sm)
+{
+    const uint32_t ty = tile / (uint32_t)a.tiles_x, tx = tile - ty * (uint32_t)a.tiles_x;
+    shoot_split<T, B, WV, JIT ? kJitter : kSharedRows, DUMP>(a, tx * 64 + (threadIdx.x & 63), ty * 4, a.wn1, a.rskip, a.wn2,
+                                                            group, sm);
+}
+
+template <int WV>
+constexpr int kSimdWaves = WV == 16 ? 4 : 6;
+
+// Six waves per SIMD (80 VGPRs, three spilled outside the lens loop): 193.0 ms on the 1e5-lens map, five (88
+// VGPRs) 196.8, eight (64, the loop spills) 201.3.  Sixteen-wave workgroups run one to a SIMD group of four.
+template <int T, int B, int WV, bool DUMP, bool JIT>
+__global__ void __launch_bounds__(64 * WV, kSimdWaves<WV>) k_split(const DirectArgs a)
+{
+    __shared__ SplitSmem<B, WV> sm;
+    split_tile<T, B, WV, DUMP, JIT>(a, blockIdx.x, blockIdx.x, sm);
+}
+
+// Persistent form over the lane blocks of a list of culling cells; see k_direct_cells for how block j of
+// cell list[i] is cut.  Workgroups take 64 blocks at a time from the counter cb.queue until none are left.
+template <int T, int B, int WV, bool JIT>
+__global__ void __launch_bounds__(64 * WV, kSimdWaves<WV>) k_split_cells(const DirectArgs a, const CellBlocks cb)
+{
+    __shared__ SplitSmem<B, WV> sm;
+    __shared__ uint32_t s_item;
+    const uint64_t n = (uint64_t)(*cb.count) * (uint64_t)cb.S;
+    for (;;) {
+        if (threadIdx.x == 0) s_item = atomicAdd(cb.queue, 1u);
+        __syncthreads();
+        const uint32_t item = s_item;
+        const uint64_t q = (uint64_t)item * 64 + (threadIdx.x & 63);
+        if ((uint64_t)item * 64 >= n) break;
+        int64_t c0 = 0, r0 = 0, cmax = 0, rmin = 0, rmax = 0;
+        if (q < n) {
+            const uint64_t i = q / (uint64_t)cb.S;
+            const int64_t j = (int64_t)(q - i * (uint64_t)cb.S);
+            const int64_t cell = cb.list[i];
+            const int64_t mx = cell % cb.ncx, my = cell / cb.ncx;
+            c0 = mx * cb.c1 + j % cb.sx;
+            rmin = my * cb.c2 + a.rskip;
+            r0 = (rmin & ~int64_t(3)) + (j / cb.sx) * 4;
+            cmax = min((mx + 1) * cb.c1, a.wn1);
+            rmax = min((my + 1) * cb.c2 + a.rskip, a.wn2);
+        }
+        shoot_split<T, B, WV, JIT ? kJitter : kOwnRows, false>(a, (uint32_t)c0, (uint32_t)r0, cmax, rmin, rmax, item, sm);
+        __syncthreads();
+    }
+}
+
+// Persistent form over a table of jobs; see k_batched.  An item is per_item consecutive blocks of its job.
+template <int T, int B, int WV>
+__global__ void __launch_bounds__(64 * WV, kSimdWaves<WV>) k_split_batched(const BatchArgs b)
+{
+    __shared__ SplitSmem<B, WV> sm;
+    __shared__ uint32_t s_item;
+    for (;;) {
+        if (threadIdx.x == 0) s_item = atomicAdd(b.queue, 1u);
+        __syncthreads();
+        const uint32_t item = s_item;
+        __syncthreads();
+        if (item >= b.n_items) break;
+        int lo = 0, hi = b.n_jobs - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (b.item_start[mid] <= item) lo = mid;
+            else hi = mid - 1;
+        }
+        const DirectArgs &a = b.jobs[lo];
+        const uint32_t first = (item - b.item_start[lo]) * a.per_item;
+        const uint32_t end = min(first + a.per_item, a.n_blocks);
+        for (uint32_t t = first; t < end; ++t) {
+            if (a.jitter)
+                split_tile<T, B, WV, false, true>(a, t, 0u, sm);
+            else
+                split_tile<T, B, WV, false, false>(a, t, 0u, sm);
+            __syncthreads();
+        }
+    }
+}
+
+template <int T, int B, int WV>
+hipError_t launch(const DirectArgs &a, hipStream_t s)
+{
+    const dim3 g(a.n_blocks), blk(64 * WV);
+    if (a.jitter) {
+        if (a.ray_y) hipLaunchKernelGGL((k_split<T, B, WV, true, true>), g, blk, 0, s, a);
+        else hipLaunchKernelGGL((k_split<T, B, WV, false, true>), g, blk, 0, s, a);
+    } else {
+        if (a.ray_y) hipLaunchKernelGGL((k_split<T, B, WV, true, false>), g, blk, 0, s, a);
+        else hipLaunchKernelGGL((k_split<T, B, WV, false, false>), g, blk, 0, s, a);
+    }
+    return hipGetLastError();
+}
+
+template <int T, int B, int WV>
+hipError_t launch_cells(const DirectArgs &a, const CellBlocks &cb, int64_t max_groups, hipStream_t s)
+{
+    int occ = 0, dev = 0, cus = 0;
+    const hipError_t e = a.jitter
+        ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_split_cells<T, B, WV, true>, 64 * WV, 0)
+        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_split_cells<T, B, WV, false>, 64 * WV, 0);
+    if (e != hipSuccess) occ = 1;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 256;
+    const dim3 g((unsigned)std::min<int64_t>((int64_t)std::max(1, occ) * std::max(1, cus), max_groups)), blk(64 * WV);
+    if (a.jitter) hipLaunchKernelGGL((k_split_cells<T, B, WV, true>), g, blk, 0, s, a, cb);
+    else hipLaunchKernelGGL((k_split_cells<T, B, WV, false>), g, blk, 0, s, a, cb);
+    return hipGetLastError();
+}
+
+template <int T, int B, int WV>
+hipError_t launch_batch(const BatchArgs &b, int grid, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_split_batched<T, B, WV>), dim3(grid), dim3(64 * WV), 0, s, b);
+    return hipGetLastError();
+}
+
+template <int T, int B, int WV>
+int occupancy_batch()
+{
+    int n = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_split_batched<T, B, WV>, 64 * WV, 0);
+    return e == hipSuccess ? n : 0;
+}
+
+}  // namespace
+
+// Call F<T, B, WV>(args) for the run length, lens tile and waves of a launch.
+#define RS_SPLIT_SWITCH(T, LT, WV, F, ...)                                     \
+    do {                                                                       \
+        if ((T) == 32) return F<32, 128, 4>(__VA_ARGS__);                      \
+        if ((T) == 16 && (LT) == 512) return F<16, 128, 4>(__VA_ARGS__);       \
+        if ((T) == 8 && (LT) == 512) return F<8, 128, 4>(__VA_ARGS__);         \
+        if ((T) == 16 && (WV) == 16) return F<16, 64, 16>(__VA_ARGS__);        \
+        if ((T) == 16 && (WV) == 8) return F<16, 64, 8>(__VA_ARGS__);          \
+        if ((T) == 16) return F<16, 64, 4>(__VA_ARGS__);                       \
+        if ((WV) == 16) return F<8, 64, 16>(__VA_ARGS__);                      \
+        if ((WV) == 8) return F<8, 64, 8>(__VA_ARGS__);                        \
+        return F<8, 64, 4>(__VA_ARGS__);                                       \
+    } while (0)
+
+hipError_t launch_split(const DirectArgs &a, int T, int LT, hipStream_t s)
+{
+    if (a.n_blocks == 0) return hipSuccess;
+    // Sixteen waves while that gives a compute unit no more than one workgroup (128^2 rays, 12800 lenses:
+    // 122 us, with eight waves 151, with four 256; but 512 x 640 rays 610, 560, 610); eight where lenses
+    // enough for all of them meet few blocks (512 x 640 rays, 400 lenses: 28.4 us against 29.3, 200 lenses
+    // 21.4 against 20.3) or the field is large (1000^2 rays, 3200 lenses: 427 us against 432, 400 lenses
+    // 67.1 against 65.8).
+    const int wv = a.n_blocks <= 256 ? 16 : (a.n_lens >= 2048 || (a.n_lens >= 256 && a.n_blocks <= 2048)) ? 8 : 4;
+    RS_SPLIT_SWITCH(T, LT, wv, launch, a, s);
+}
+
+hipError_t launch_split_cells(const DirectArgs &a, int T, int LT, const CellBlocks &cb, int64_t blocks, hipStream_t s)
+{
+    const int64_t groups = (blocks + 63) / 64;
+    if (groups <= 0) return hipSuccess;
+    const int wv = a.n_lens >= 2048 ? 8 : 4;
+    RS_SPLIT_SWITCH(T, LT, wv, launch_cells, a, cb, groups, s);
+}
+
+int split_batched_waves(int64_t most_lenses) { return most_lenses >= 2048 ? 8 : 4; }
+
+hipError_t launch_split_batched(const BatchArgs &b, int T, int LT, int WV, int grid, hipStream_t s)
+{
+    RS_SPLIT_SWITCH(T, LT, WV, launch_batch, b, grid, s);
+}
+
+int split_batched_occupancy(int T, int LT, int WV) { RS_SPLIT_SWITCH(T, LT, WV, occupancy_batch); }
+
+}  // namespace rs
