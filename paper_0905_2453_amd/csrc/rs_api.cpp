@@ -1023,9 +1023,10 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     uint32_t *stats = reinterpret_cast<uint32_t *>(base);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // statistics: [0] kept cells (the list length), [1] cells, [2] lane blocks per cell,
-    // [3] rays per lane block, [4 + l] kept cells of the coarser level l < levels - 1, [8] work counter
+    // [3] rays per lane block, [4 + l] kept cells of the coarser level l < levels - 1, [8] work counter of
+    // the shoot, [kZoomQueue + l] of level l
     static_assert(rs::kZoomLevels <= 5, "the statistics block holds four coarser levels");
-    hipError_t e = rs::launch_fill_u32(stats, 9, 0u, s);
+    hipError_t e = rs::launch_fill_u32(stats, rs::kZoomQueue + rs::kZoomLevels, 0u, s);
     if (e == hipSuccess) e = rs::launch_fill_u32(stats + 1, 1, (uint32_t)L.cells, s);
     if (e == hipSuccess) e = rs::launch_fill_u32(stats + 2, 1, (uint32_t)L.S, s);
     if (e == hipSuccess) e = rs::launch_fill_u32(stats + 3, 1, (uint32_t)(t.K1 * t.K2), s);

@@ -164,6 +164,7 @@ hipError_t launch_ff_eval(const FarArgs &f, const CellArgs &g, hipStream_t s);
 // ---------------------------------------------------------------- zoom
 
 constexpr int kZoomLevels = 5;   // culling levels, each halving the cell side of the one above
+constexpr int kZoomQueue = 9;    // work counters of the levels in the statistics block
 
 struct ZoomArgs {
     const float4 *lenses;
@@ -182,7 +183,8 @@ struct ZoomArgs {
     double time;
     uint32_t *lists[kZoomLevels];       // kept cells of each level; the last is `list`
     uint32_t *list;                     // kept cell indices (finest level)
-    uint32_t *stats;                    // [0] cells kept (list length), [4 + l] kept at level l < levels - 1
+    uint32_t *stats;                    // [0] cells kept (list length), [4 + l] kept at level l < levels - 1,
+                                        // [kZoomQueue + l] work counter of level l
 };
 
 hipError_t launch_zoom_mark(const ZoomArgs &z, hipStream_t s);
