@@ -302,7 +302,11 @@ __device__ __forceinline__ void forward32(const uint16_t *Wbf, const float *sbia
 // time the result goes into the model's tile header.  For a moving field (eval with
 // velocities) the far set is still the one chosen by the fit-time positions, each far lens
 // enters at its position at f.time, and the result goes to f.affine (only the evaluated tiles).
-template <int NT>
+// SPLIT (moving field, few tiles): S = gridDim.y workgroups share a tile, workgroup y taking lenses
+// 256 y + t + 256 S k; their sums go to f.affine_part and k_ff_affine_sum adds them in order.  One workgroup
+// per tile leaves the GPU idle below a thousand tiles: 48 tiles, 1e6 lenses: 2375 us, split
+// over 42 workgroups each 124.
+template <int NT, bool SPLIT>
 __global__ void __launch_bounds__(256) k_ff_affine(const FarArgs f)
 {
     constexpr int kAffTiles = NT;
@@ -338,7 +342,8 @@ __global__ void __launch_bounds__(256) k_ff_affine(const FarArgs f)
     double a1[kAffTiles], a2[kAffTiles], j11[kAffTiles], j12[kAffTiles];
 #pragma unroll
     for (int t = 0; t < kAffTiles; ++t) a1[t] = a2[t] = j11[t] = j12[t] = 0.0;
-    for (int64_t i = threadIdx.x; i < f.n_lens; i += 256) {
+    const int64_t step = SPLIT ? 256 * (int64_t)gridDim.y : 256;
+    for (int64_t i = threadIdx.x + (SPLIT ? 256 * (int64_t)blockIdx.y : 0); i < f.n_lens; i += step) {
         const float4 l0 = f.lenses[i];
         const float4 l = moved_lens(l0, f.vel, i, f.time);
         const bool near_group = is_near(l0.x, l0.y, ulo, uhi, rn2);
@@ -372,7 +377,9 @@ __global__ void __launch_bounds__(256) k_ff_affine(const FarArgs f)
                 for (int k = 0; k < 4; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + s];
             __syncthreads();
         }
-        if (threadIdx.x == 0 && f.affine) {
+        if (SPLIT && threadIdx.x < 4) {
+            f.affine_part[4 * ((size_t)(first + t) * gridDim.y + blockIdx.y) + threadIdx.x] = red[threadIdx.x][0];
+        } else if (threadIdx.x == 0 && f.affine) {
             double *o = f.affine + 8 * (size_t)tile[t];
             o[0] = red[0][0];
             o[1] = red[1][0];
@@ -393,6 +400,27 @@ __global__ void __launch_bounds__(256) k_ff_affine(const FarArgs f)
             h[9] = 1.0;
         }
         __syncthreads();   // red[] is reused by the next tile
+    }
+}
+
+// The sums of a tile's `parts` (at most 64) workgroups, added by one wave per tile in a fixed tree.
+__global__ void __launch_bounds__(64) k_ff_affine_sum(const FarArgs f, int parts)
+{
+    const uint32_t tile = f.eval_tiles ? (uint32_t)f.eval_tiles[blockIdx.x] : blockIdx.x;
+    const int lane = threadIdx.x;
+    double v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] = lane < parts ? f.affine_part[4 * ((size_t)blockIdx.x * parts + lane) + k] : 0.0;
+        for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o);
+    }
+    if (lane == 0) {
+        double *o = f.affine + 8 * (size_t)tile;
+        o[0] = v[0];
+        o[1] = v[1];
+        o[2] = v[2];
+        o[3] = v[3];
+        o[4] = -v[2];
     }
 }
 
@@ -1271,11 +1299,14 @@ __global__ void k_write_model_header(uint8_t *model, uint64_t hash, int64_t n_ti
 
 // *out += sum over lens records i of mix64(bits of (x1, x2) + (i + 1) G) + mix64(bits of (m, pad) ^ i):
 // a checksum of the lens array that does not depend on the order of the additions (wrapping
-// 64-bit sums), one atomic per wave.
-__global__ void __launch_bounds__(256) k_lens_checksum(const float4 *lenses, int64_t n, unsigned long long *out)
+// 64-bit sums).  Additions to one address complete one after the other, about 12 ns each, so a workgroup adds
+// once and few workgroups are launched (1e6 lenses: one addition per wave of 2048 workgroups took 102 us, now 7.7).
+__global__ void __launch_bounds__(1024) k_lens_checksum(const float4 *lenses, int64_t n, unsigned long long *out)
 {
+    __shared__ unsigned long long s_acc[16];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     unsigned long long acc = 0;
+#pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         const uint4 v = reinterpret_cast<const uint4 *>(lenses)[i];
         const uint64_t a = ((uint64_t)v.y << 32) | v.x, b = ((uint64_t)v.w << 32) | v.z;
@@ -1283,7 +1314,13 @@ __global__ void __launch_bounds__(256) k_lens_checksum(const float4 *lenses, int
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if ((threadIdx.x & 63) == 0 && acc) atomicAdd(out, acc);
+    if ((threadIdx.x & 63) == 0) s_acc[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long t = 0;
+        for (int w = 0; w < 16; ++w) t += s_acc[w];
+        if (t) atomicAdd(out, t);
+    }
 }
 
 }  // namespace
@@ -1291,19 +1328,27 @@ __global__ void __launch_bounds__(256) k_lens_checksum(const float4 *lenses, int
 hipError_t launch_lens_checksum(const float4 *lenses, int64_t n, unsigned long long *out, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    const int64_t blocks = std::min<int64_t>(2048, (n + 255) / 256);
-    hipLaunchKernelGGL(k_lens_checksum, dim3((unsigned)blocks), dim3(256), 0, s, lenses, n, out);
+    const int64_t blocks = std::min<int64_t>(256, (n + 1023) / 1024);
+    hipLaunchKernelGGL(k_lens_checksum, dim3((unsigned)blocks), dim3(1024), 0, s, lenses, n, out);
     return hipGetLastError();
 }
 
-// affine bases of `count` tiles: four per workgroup once there are at least 8192 (2048
-// workgroups), else one per workgroup (the sums are the same either way)
+// affine bases of `count` tiles: four per workgroup once there are at least 8192 (2048 workgroups), else one
+// per workgroup (the sums are the same either way), and below 1024 tiles of a moving field so many workgroups
+// per tile that about kAffineParts run
 hipError_t launch_affine(const FarArgs &f, int64_t count, hipStream_t s)
 {
-    if (count >= 8192)
-        hipLaunchKernelGGL(k_ff_affine<4>, dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s, f);
-    else
-        hipLaunchKernelGGL(k_ff_affine<1>, dim3((unsigned)count), dim3(256), 0, s, f);
+    const int parts = f.affine ? (int)std::min<int64_t>({64, kAffineParts / count, (f.n_lens + 255) / 256}) : 1;
+    if (count >= 8192) {
+        hipLaunchKernelGGL((k_ff_affine<4, false>), dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s, f);
+    } else if (parts < 2) {
+        hipLaunchKernelGGL((k_ff_affine<1, false>), dim3((unsigned)count), dim3(256), 0, s, f);
+    } else {
+        hipLaunchKernelGGL((k_ff_affine<1, true>), dim3((unsigned)count, (unsigned)parts), dim3(256), 0, s, f);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_ff_affine_sum, dim3((unsigned)count), dim3(64), 0, s, f, parts);
+    }
     return hipGetLastError();
 }
 

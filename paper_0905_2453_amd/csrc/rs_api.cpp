@@ -562,21 +562,31 @@ int shoot_with_partials(const rs_job *job, const Tune &t, uint32_t *part, hipStr
     return RS_OK;
 }
 
+// Offsets in the eval workspace: cell counts and cursors at 0, then the cell starts, the lens lists, the
+// affine bases, the sums they are added up from, and the lens checksum word.
+struct EvalLayout {
+    size_t cursor, start, idx, affine, part, checksum, total;
+};
+
+EvalLayout eval_layout(const rs_job *job, const FarGeom &g, size_t cells)
+{
+    EvalLayout L{};
+    L.cursor = align256(cells * 4);
+    L.start = 2 * L.cursor;
+    L.idx = L.start + align256((cells + 1) * 4);
+    L.affine = L.idx + align256((size_t)std::max<int64_t>(job->n_lens, 1) * 4);
+    L.part = L.affine + align256((size_t)g.n_tiles * 8 * sizeof(double));
+    L.checksum = L.part + (size_t)rs::kAffineParts * 4 * sizeof(double);
+    L.total = L.checksum + 256 + 256;
+    return L;
+}
+
 size_t eval_ws_bytes(const rs_job *job, const rs_ff_config *c, const FarGeom &g)
 {
     double ox, oy;
     int64_t ncx, ncy;
     cell_geom(job, c, g, ox, oy, ncx, ncy);
-    const size_t cells = (size_t)(ncx * ncy);
-    return align256(cells * 4) * 2 + align256((cells + 1) * 4) + align256((size_t)std::max<int64_t>(job->n_lens, 1) * 4) +
-           align256((size_t)g.n_tiles * 8 * sizeof(double)) + 256 + 256;
-}
-
-// Offset of the lens checksum word in the eval workspace (after the cell lists and affine bases).
-size_t eval_checksum_off(const rs_job *job, const FarGeom &g, size_t cells)
-{
-    return align256(cells * 4) * 2 + align256((cells + 1) * 4) + align256((size_t)std::max<int64_t>(job->n_lens, 1) * 4) +
-           align256((size_t)g.n_tiles * 8 * sizeof(double));
+    return eval_layout(job, g, (size_t)(ncx * ncy)).total;
 }
 
 }  // namespace
@@ -941,7 +951,8 @@ int rs_farfield_eval(const rs_job *job, const rs_ff_config *cfg, const void *mod
     // ... and on this lens array: its checksum, computed now, must equal the one the fit stored
     uint8_t *base = reinterpret_cast<uint8_t *>(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
     const size_t cells = (size_t)(ncx * ncy);
-    uint64_t *csum = reinterpret_cast<uint64_t *>(base + eval_checksum_off(job, g, cells));
+    const EvalLayout L = eval_layout(job, g, cells);
+    uint64_t *csum = reinterpret_cast<uint64_t *>(base + L.checksum);
     uint64_t hdr[6] = {0, 0, 0, 0, 0, 0}, lens_sum = 0;
     std::vector<int32_t> tl(cfg->eval_tiles ? (size_t)cfg->n_eval_tiles : 0);
     hipError_t e = rs::launch_fill_u32(reinterpret_cast<uint32_t *>(csum), 2, 0u, s);
@@ -981,14 +992,14 @@ int rs_farfield_eval(const rs_job *job, const rs_ff_config *cfg, const void *mod
     cg.ncy = (int32_t)ncy;
     cg.n_cells = (int32_t)cells;
     cg.count = reinterpret_cast<int32_t *>(base);
-    cg.cursor = reinterpret_cast<int32_t *>(base + align256(cells * 4));
-    cg.start = reinterpret_cast<int32_t *>(base + 2 * align256(cells * 4));
-    cg.idx = reinterpret_cast<int32_t *>(base + 2 * align256(cells * 4) + align256((cells + 1) * 4));
+    cg.cursor = reinterpret_cast<int32_t *>(base + L.cursor);
+    cg.start = reinterpret_cast<int32_t *>(base + L.start);
+    cg.idx = reinterpret_cast<int32_t *>(base + L.idx);
     if (job->velocities) {
         f.vel = reinterpret_cast<const float2 *>(job->velocities);
         f.time = job->time;
-        f.affine = reinterpret_cast<double *>(base + 2 * align256(cells * 4) + align256((cells + 1) * 4) +
-                                              align256((size_t)std::max<int64_t>(job->n_lens, 1) * 4));
+        f.affine = reinterpret_cast<double *>(base + L.affine);
+        f.affine_part = reinterpret_cast<double *>(base + L.part);
     }
     e = rs::launch_zero(reinterpret_cast<uint32_t *>(base), (int64_t)(2 * align256(cells * 4) / 4), s);
     if (e == hipSuccess) e = rs::launch_ff_eval(f, cg, s);

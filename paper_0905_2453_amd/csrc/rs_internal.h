@@ -108,6 +108,9 @@ constexpr size_t kTileBiasOff = ((size_t)kNParams * 2 + 15) / 16 * 16;
 constexpr size_t kTileRecord = (kTileWeightsOff + kTileBiasOff + 130 * 4 + 255) / 256 * 256;
 constexpr uint64_t kModelMagic = 0x3130304646535252ull;  // "RRSFF001"
 
+// Workgroups that share the affine bases of a moving field's few tiles.
+constexpr int kAffineParts = 2048;
+
 struct FarArgs {
     const float4 *lenses;
     int64_t n_lens;
@@ -141,6 +144,7 @@ struct FarArgs {
     const float2 *vel;            // moving field (eval only): lens velocities, or null
     double time;
     double *affine;               // moving field: refreshed affine bases, n_tiles x 8 doubles
+    double *affine_part;          // ... and the sums of the workgroups of a tile, at most kAffineParts x 4 doubles
     int64_t n_eval;
     int64_t gn1;                  // full grid width, jitter keys and switch (as DirectArgs)
     uint64_t jkey1, jkey2;
