@@ -1120,21 +1120,37 @@ __global__ void k_cells_sort(const CellArgs g)
 // ---------------------------------------------------------------- eval: surrogate
 
 // `splits` workgroups per fit tile, workgroup q taking passes q, q + splits, ... of the tile's
-// rays (every ray is computed the same way whatever the split).  Rays go 128 at a time (32 per
-// wave, a lane pair per ray): far
-// field from the affine base plus the network (layers 1-2 on MFMA), near field summed exactly
-// over the candidate lenses of the cells around the tile (far ones masked to zero-mass
-// padding), the two lanes of a ray splitting the lenses; then the FP64 lens equation and
-// wave-aggregated binning into the job's map.
-template <bool DUMP>
-__global__ void __launch_bounds__(256) k_surrogate(const FarArgs f, const CellArgs g, int splits)
+// rays (every ray is computed the same way whatever the split).  A lane holds four rays of a column
+// (rows 4 r .. 4 r + 3 of the tile), so a pass shoots 1024 rays:
+//   far field: affine base plus the network (on MFMA, 32 rays at a time, a lane pair per ray; the
+//     coordinates and outputs change lanes through LDS);
+//   near field: summed exactly, one reciprocal per ray and lens, over the candidate lenses of the cells
+//     around the tile in float32 runs of 16 candidates, each run added in FP64;
+// then the FP64 lens equation and wave-aggregated binning into the job's map.
+//
+// Bound: the issue of its VALU instructions (a reciprocal counts five), about half of them the near field.  Of the
+// candidates a third are out of reach (the corners of the cells' box): staging keeps only the near ones of
+// a run, filled up to a multiple of four with lenses without mass, which add exact zeros, so a run's sum is that
+// of all sixteen.  Four rays per lane share x1 - x1_i and its square (cell-centred rays) and each LDS read.
+// 4096^2 rays in 64^2 tiles, about 200 near lenses: 1.24 ms; one ray per lane pair, all candidates: 2.03.
+constexpr int kNearCap = 1024, kNearRun = 16;
+
+struct NearStage {
+    float4 lens[kNearCap];                    // the batch's candidates, then its runs without the far ones
+    uint16_t start[kNearCap / kNearRun + 2];  // first lens of each run; the entry after the last ends it
+};
+
+template <bool DUMP, bool JIT>
+__global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const CellArgs g, int splits)
 {
-    constexpr int CAP = 2048, T = 16;
+    constexpr int CAP = kNearCap, T = kNearRun, NX = JIT ? 4 : 1;
     __shared__ __attribute__((aligned(16))) uint16_t Wbf[kNParamsPad];
     __shared__ __attribute__((aligned(16))) float sbias[130];
-    __shared__ float4 s_near[CAP];
+    __shared__ NearStage s_near;
+    __shared__ float2 s_net[4][4][64];   // per wave and row: the rays' tile coordinates, then the network outputs
     __shared__ __attribute__((aligned(16))) uint32_t s_zero[4];
     __shared__ int s_cells[4];
+    __shared__ int2 s_rows[64];
     __shared__ uint32_t s_lost;
 
     const uint32_t item = blockIdx.x / (uint32_t)splits, split = blockIdx.x % (uint32_t)splits;
@@ -1147,7 +1163,6 @@ __global__ void __launch_bounds__(256) k_surrogate(const FarArgs f, const CellAr
     const double *hd = tile_hdr(f, tile);
     // a moving field uses the affine base refreshed at f.time; the network residual is the fitted one
     const double *ab = f.affine ? f.affine + 8 * (size_t)tile : hd + 4;
-    const double a01 = ab[0], a02 = ab[1], j11 = ab[2], j12 = ab[3], j22 = ab[4], st = hd[9];
     const uint16_t *wsrc = tile_w(f, tile);
     const float *bsrc = reinterpret_cast<const float *>(reinterpret_cast<const uint8_t *>(wsrc) + kTileBiasOff);
     for (int p = tid; p < kNParams; p += 256) Wbf[wslot(p)] = wsrc[p];
@@ -1164,120 +1179,216 @@ __global__ void __launch_bounds__(256) k_surrogate(const FarArgs f, const CellAr
     __syncthreads();
     const int cx0 = s_cells[0], cx1 = s_cells[1], cy0 = s_cells[2], cy1 = s_cells[3];
     const int ncx = max(0, cx1 - cx0 + 1);
-    const int n_rows = max(0, cy1 - cy0 + 1);
+    const int n_rows = ncx > 0 ? max(0, cy1 - cy0 + 1) : 0;
     // candidate lenses are the concatenation of cell rows cy0..cy1, each the contiguous index
     // range start[cy * ncx_grid + cx0] .. start[cy * ncx_grid + cx1 + 1]
+    // (the first index of each row and the number of candidates up to its end are kept in LDS while the rows are
+    // few)
     int n_cand = 0;
-    for (int r = 0; r < n_rows; ++r) {
-        const int row = (cy0 + r) * g.ncx;
-        n_cand += g.start[row + cx1 + 1] - g.start[row + cx0];
+    const bool rows_in_lds = n_rows <= 64;
+    if (rows_in_lds) {
+        if (wave == 0) {
+            const int row = (cy0 + min(lane, max(n_rows - 1, 0))) * g.ncx;
+            const int first = n_rows > 0 ? g.start[row + cx0] : 0;
+            int end = lane < n_rows ? g.start[row + cx1 + 1] - first : 0;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(end, o);
+                if (lane >= o) end += v;
+            }
+            s_rows[lane] = make_int2(first, end);
+        }
+        __syncthreads();
+        n_cand = s_rows[63].y;
+    } else {
+        for (int r = 0; r < n_rows; ++r) {
+            const int row = (cy0 + r) * g.ncx;
+            n_cand += g.start[row + cx1 + 1] - g.start[row + cx0];
+        }
     }
+    // position in g.idx of candidate e < n_cand
+    auto index_of = [&](int e) -> int {
+        if (rows_in_lds) {
+            int before = 0;
+            for (int r = 0;; ++r) {
+                const int2 v = s_rows[r];
+                if (e < v.y) return v.x + e - before;
+                before = v.y;
+            }
+        }
+        for (int r = 0;; ++r) {
+            const int row = (cy0 + r) * g.ncx, len = g.start[row + cx1 + 1] - g.start[row + cx0];
+            if (e < len) return g.start[row + cx0] + e;
+            e -= len;
+        }
+    };
     const double rn2 = f.r_near * f.r_near;
     const int n_batches = (n_cand + CAP - 1) / CAP;
 
-    // stage candidates [b CAP, b CAP + CAP) (far ones become zero-mass padding)
+    // Stage the runs of candidates [b CAP, b CAP + CAP): first the candidates as they come with the number of near
+    // ones per run (a run is 16 lanes of a wave), then, the places known, each near one moved to its run's next
+    // place.  Places only move down, so a group of 256 read before it is written never overtakes the next.
     auto stage = [&](int b) {
-        const int base = b * CAP;
-        for (int k = tid; k < CAP; k += 256) {
-            float4 v = make_float4(kPadCoord, kPadCoord, 0.f, 0.f);
-            int e = base + k;
-            if (e < n_cand) {
-                for (int r = 0; r < n_rows; ++r) {
-                    const int row = (cy0 + r) * g.ncx;
-                    const int len = g.start[row + cx1 + 1] - g.start[row + cx0];
-                    if (e < len) {
-                        // near set by fit-time position; a moving lens enters at its position at f.time
-                        const int li = g.idx[g.start[row + cx0] + e];
-                        const float4 l = g.lenses[li];
-                        if (is_near(l.x, l.y, lo, hi, rn2)) v = moved_lens(l, f.vel, li, f.time);
-                        break;
-                    }
-                    e -= len;
+        const int nb = min(CAP, n_cand - b * CAP), runs = (nb + T - 1) / T;
+        for (int k = tid; k < (nb + 255) / 256 * 256; k += 256) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k < nb) {
+                // near set by fit-time position; a moving lens enters at its position at f.time
+                const int li = g.idx[index_of(b * CAP + k)];
+                const float4 l = f.lenses[li];
+                if (is_near(l.x, l.y, lo, hi, rn2)) {
+                    v = moved_lens(l, f.vel, li, f.time);
+                    v.w = 1.f;
                 }
             }
-            s_near[k] = v;
+            s_near.lens[k] = v;
+            const uint32_t in_run = (uint32_t)(__ballot(v.w != 0.f) >> (lane & 48)) & 0xffffu;
+            if ((lane & 15) == 0 && k / T < runs) s_near.start[k / T] = (uint16_t)((__popc(in_run) + 1) & ~1);
+        }
+        __syncthreads();
+        if (wave == 0) {
+            // exclusive scan of the runs' lengths, two per lane
+            static_assert(CAP / T <= 128, "two runs per lane");
+            const int a0 = 2 * lane < runs ? s_near.start[2 * lane] : 0, a1 = 2 * lane + 1 < runs ? s_near.start[2 * lane + 1] : 0;
+            int sum = a0 + a1;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(sum, o);
+                if (lane >= o) sum += v;
+            }
+            const int before = sum - a0 - a1;
+            if (2 * lane <= runs) s_near.start[2 * lane] = (uint16_t)before;
+            if (2 * lane + 1 <= runs) s_near.start[2 * lane + 1] = (uint16_t)(before + a0);
+            if (lane == 63 && runs == 128) s_near.start[128] = (uint16_t)sum;
+        }
+        __syncthreads();
+        for (int k = tid; k < (nb + 255) / 256 * 256; k += 256) {
+            float4 v = s_near.lens[k];
+            const uint32_t in_run = (uint32_t)(__ballot(v.w != 0.f) >> (lane & 48)) & 0xffffu;
+            const int l16 = lane & 15, cnt = __popc(in_run), pads = cnt & 1;
+            const int at = k / T < runs ? s_near.start[k / T] : 0;
+            __syncthreads();
+            if (k / T < runs) {
+                if (v.w != 0.f) s_near.lens[at + __popc(in_run & ((1u << l16) - 1u))] = v;
+                if (l16 < pads) s_near.lens[at + cnt + l16] = make_float4(kPadCoord, kPadCoord, 0.f, 0.f);
+            }
         }
     };
     if (n_batches == 1) stage(0);
     __syncthreads();
 
-    const int n_rays = n[0] * n[1];
-    const int passes = (f.TX * f.TY + 127) / 128;
+    const int quads = n[0] * ((n[1] + 3) / 4);   // blocks of four rays of a column
+    const int passes = (quads + 255) / 256;
     for (int ps = (int)split; ps < passes; ps += splits) {
-        const int ri = 128 * ps + 32 * wave + col;
-        const int ix = ri % f.TX, iy = ri / f.TX;
-        const bool active = ri < f.TX * f.TY && ix < n[0] && iy < n[1];
-        const int64_t g1 = i0[0] + ix, g2 = i0[1] + iy, rg = g2 * f.gn1 + g1;
-        const float x1 = ray_coord(f.glo1, f.gt1, g1, f.jitter ? jitter_u(f.jkey1, rg) : 0.5);
-        const float x2 = ray_coord(f.glo2, f.gt2, g2, f.jitter ? jitter_u(f.jkey2, rg) : 0.5);
-        // far field: network
-        float o0 = 0.f, o1 = 0.f;
-        if (!f.affine_only) {
-            const float u = hf == 0 ? (float)(((double)x1 - c[0]) / hw[0]) : (float)(((double)x2 - c[1]) / hw[1]);
-            uint32_t phi4[4];
-            features8(u, phi4);
-            Fwd fw;
-            forward32<false>(Wbf, sbias, reinterpret_cast<const uint16_t *>(s_zero), phi4, lane, fw);
-            o0 = fw.o[0];
-            o1 = fw.o[1];
+        const int qi = 256 * ps + 64 * wave + lane;
+        const int ix = qi % n[0], iy = qi / n[0] * 4;
+        const int64_t g1 = i0[0] + ix;
+        float x1[NX], x2[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t g2 = i0[1] + iy + e, rg = g2 * f.gn1 + g1;
+            if (e < NX) x1[e] = ray_coord(f.glo1, f.gt1, g1, JIT ? jitter_u(f.jkey1, rg) : 0.5);
+            x2[e] = ray_coord(f.glo2, f.gt2, g2, JIT ? jitter_u(f.jkey2, rg) : 0.5);
         }
-        // near field: this lane takes half hf of every staged batch
-        double A1 = 0.0, A2 = 0.0;
+        // far field: network, 32 rays of a row at a time; the outputs come in the half-0 lanes
+        float2 (*net)[64] = s_net[wave];
+        if (!f.affine_only) {
+            float u1 = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (e < NX) u1 = (float)(((double)x1[e] - c[0]) / hw[0]);
+                net[e][lane] = make_float2(u1, (float)(((double)x2[e] - c[1]) / hw[1]));
+            }
+            wave_sync();
+#pragma unroll 1
+            for (int k = 0; k < 8; ++k) {
+                float2 *ray = &net[k >> 1][32 * (k & 1) + col];
+                const float2 u = *ray;
+                uint32_t phi4[4];
+                features8(hf == 0 ? u.x : u.y, phi4);
+                Fwd fw;
+                forward32<false>(Wbf, sbias, reinterpret_cast<const uint16_t *>(s_zero), phi4, lane, fw);
+                wave_sync();
+                if (hf == 0) *ray = make_float2(fw.o[0], fw.o[1]);
+                wave_sync();
+            }
+        }
+        // near field
+        double A1[4] = {}, A2[4] = {};
         for (int b = 0; b < n_batches; ++b) {
             if (n_batches > 1) {
                 __syncthreads();
                 stage(b);
                 __syncthreads();
             }
-            // the two lanes of a ray split the batch: [0, half) and [half, nb), in runs of T
-            const int nb = min(CAP, n_cand - b * CAP);
-            const int half = ((nb + 1) / 2 + T - 1) / T * T;
-            const float4 *L = s_near + (hf ? half : 0);
-            const int m = hf ? max(0, nb - half) : min(half, nb);
-            const int mr = (m + T - 1) / T * T;
-            for (int r = 0; r < mr; r += T) {
-                float s1 = 0.f, s2 = 0.f;
+            const int runs = (min(CAP, n_cand - b * CAP) + T - 1) / T;
+            int at = 0;
+            for (int r = 0; r < runs; ++r) {
+                const int end = __builtin_amdgcn_readfirstlane((int)s_near.start[r + 1]);
+                if (at == end) continue;      // no near lens: the run's sum is zero
+                float s1[4] = {}, s2[4] = {};
+                auto add = [&](int k) __attribute__((always_inline)) {
+                    const float4 l = s_near.lens[k];
+                    float dx[NX], dx2[NX];
 #pragma unroll
-                for (int j = 0; j < T; ++j) {
-                    const float4 l = L[r + j];
-                    const float dx = x1 - l.x, dy = x2 - l.y;
-                    const float d = l.z * __builtin_amdgcn_rcpf(fmaf(dy, dy, dx * dx));
-                    s1 = fmaf(d, dx, s1);
-                    s2 = fmaf(d, dy, s2);
+                    for (int e = 0; e < NX; ++e) {
+                        dx[e] = x1[e] - l.x;
+                        dx2[e] = dx[e] * dx[e];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float dy = x2[e] - l.y;
+                        const float d = l.z * __builtin_amdgcn_rcpf(fmaf(dy, dy, dx2[JIT ? e : 0]));
+                        s1[e] = fmaf(d, dx[JIT ? e : 0], s1[e]);
+                        s2[e] = fmaf(d, dy, s2[e]);
+                    }
+                };
+                for (; at + 4 <= end; at += 4) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) add(at + j);
                 }
-                A1 += (double)s1;
-                A2 += (double)s2;
+                if (at < end) {
+                    add(at);
+                    add(at + 1);
+                    at += 2;
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    A1[e] += (double)s1[e];
+                    A2[e] += (double)s2[e];
+                }
             }
         }
-        const double B1 = __shfl_xor(A1, 32), B2 = __shfl_xor(A2, 32);
-        const double N1 = (hf == 0 ? A1 + B1 : B1 + A1) * kRcpBiasComp;
-        const double N2 = (hf == 0 ? A2 + B2 : B2 + A2) * kRcpBiasComp;
-        const double d1 = (double)x1 - c[0], d2 = (double)x2 - c[1];
-        const double F1 = a01 + j11 * d1 + j12 * d2 + st * (double)o0;
-        const double F2 = a02 + j12 * d1 + j22 * d2 + st * (double)o1;
-        const double y1 = f.lam1 * (double)x1 - (F1 + N1);
-        const double y2 = f.lam2 * (double)x2 - (F2 + N2);
-        int key = -2;
-        if (active && hf == 0) {
-            const double p1 = floor((y1 - f.mlo1) * f.ms1), p2 = floor((y2 - f.mlo2) * f.ms2);
-            key = (p1 >= 0.0 && p1 < (double)f.mn1 && p2 >= 0.0 && p2 < (double)f.mn2) ? (int)p2 * f.mn1 + (int)p1 : -1;
-            if (DUMP) {
-                const int64_t rw = (i0[1] + iy - f.wlo2) * f.wn1 + (i0[0] + ix - f.wlo1);
-                f.ray_y[2 * rw] = y1;
-                f.ray_y[2 * rw + 1] = y2;
-                f.ray_pix[rw] = key;
+        const double a01 = ab[0], a02 = ab[1], j11 = ab[2], j12 = ab[3], j22 = ab[4], st = hd[9];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float2 o = f.affine_only ? make_float2(0.f, 0.f) : net[e][lane];
+            const double X1 = (double)x1[JIT ? e : 0], X2 = (double)x2[e];
+            const double d1 = X1 - c[0], d2 = X2 - c[1];
+            const double F1 = a01 + j11 * d1 + j12 * d2 + st * (double)o.x;
+            const double F2 = a02 + j12 * d1 + j22 * d2 + st * (double)o.y;
+            const double y1 = f.lam1 * X1 - (F1 + A1[e] * kRcpBiasComp);
+            const double y2 = f.lam2 * X2 - (F2 + A2[e] * kRcpBiasComp);
+            int key = -2;
+            if (qi < quads && iy + e < n[1]) {
+                const double p1 = floor((y1 - f.mlo1) * f.ms1), p2 = floor((y2 - f.mlo2) * f.ms2);
+                key = (p1 >= 0.0 && p1 < (double)f.mn1 && p2 >= 0.0 && p2 < (double)f.mn2) ? (int)p2 * f.mn1 + (int)p1 : -1;
+                if (DUMP) {
+                    const int64_t rw = (i0[1] + iy + e - f.wlo2) * f.wn1 + (i0[0] + ix - f.wlo1);
+                    f.ray_y[2 * rw] = y1;
+                    f.ray_y[2 * rw + 1] = y2;
+                    f.ray_pix[rw] = key;
+                }
             }
+            // runs of equal keys over consecutive lanes are added once
+            const int prev = __shfl_up(key, 1);
+            const bool head = (lane == 0) || (key != prev);
+            const unsigned long long H = __ballot(head);
+            const unsigned long long above = lane == 63 ? 0ull : (H >> (lane + 1));
+            const int nxt = above ? lane + 1 + __builtin_ctzll(above) : 64;
+            if (head && key >= 0) atomicAdd(&f.counts[key], (uint32_t)(nxt - lane));
+            if (head && key == -1) atomicAdd(&s_lost, (uint32_t)(nxt - lane));
         }
-        // runs of equal keys over consecutive lanes are added once
-        const int prev = __shfl_up(key, 1);
-        const bool head = (lane == 0) || (key != prev);
-        const unsigned long long H = __ballot(head);
-        const unsigned long long above = lane == 63 ? 0ull : (H >> (lane + 1));
-        const int nxt = above ? lane + 1 + __builtin_ctzll(above) : 64;
-        if (head && key >= 0) atomicAdd(&f.counts[key], (uint32_t)(nxt - lane));
-        if (head && key == -1) atomicAdd(&s_lost, (uint32_t)(nxt - lane));
+        wave_sync();   // the outputs are read before the next pass writes its coordinates
     }
-    (void)n_rays;
     __syncthreads();
     if (tid == 0 && s_lost) atomicAdd(f.lost, (unsigned long long)s_lost);
 }
@@ -1396,13 +1507,19 @@ hipError_t launch_ff_eval(const FarArgs &f, const CellArgs &g, hipStream_t s)
     if (f.affine) {
         if ((e = launch_affine(f, grid, s)) != hipSuccess) return e;
     }
-    // large tiles are few: split their rays over up to 8 workgroups so that about 4096 run
-    const int passes = (f.TX * f.TY + 127) / 128;
-    const int splits = (int)std::max<int64_t>(1, std::min<int64_t>({8, passes, (4096 + grid - 1) / grid}));
-    if (f.ray_y)
-        hipLaunchKernelGGL((k_surrogate<true>), dim3(grid * (uint32_t)splits), dim3(256), 0, s, f, g, splits);
-    else
-        hipLaunchKernelGGL((k_surrogate<false>), dim3(grid * (uint32_t)splits), dim3(256), 0, s, f, g, splits);
+    // few tiles: their rays split over so many workgroups that about 4096 run, each with at least one pass (a
+    // workgroup's staging costs a tenth of a pass: 4 tiles of 1024^2 rays over 1024 workgroups each 0.89 ms, over
+    // 32 2.4, over 8 9.4; 256 tiles of 256^2 over 16 1.57 ms, over 8 1.64)
+    const int64_t passes = ((int64_t)f.TX * ((f.TY + 3) / 4) + 255) / 256;
+    const int splits = (int)std::max<int64_t>(1, std::min<int64_t>(passes, (4096 + grid - 1) / grid));
+    const dim3 gr(grid * (uint32_t)splits), blk(256);
+    if (f.jitter) {
+        if (f.ray_y) hipLaunchKernelGGL((k_surrogate<true, true>), gr, blk, 0, s, f, g, splits);
+        else hipLaunchKernelGGL((k_surrogate<false, true>), gr, blk, 0, s, f, g, splits);
+    } else {
+        if (f.ray_y) hipLaunchKernelGGL((k_surrogate<true, false>), gr, blk, 0, s, f, g, splits);
+        else hipLaunchKernelGGL((k_surrogate<false, false>), gr, blk, 0, s, f, g, splits);
+    }
     return hipGetLastError();
 }
 
