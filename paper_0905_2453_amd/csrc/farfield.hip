@@ -424,38 +424,158 @@ __global__ void __launch_bounds__(64) k_ff_affine_sum(const FarArgs f, int parts
     }
 }
 
+// Orders a wave's own LDS stores and loads (LDS performs them in order; this keeps the compiler to it).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------- fit: exact far-field samples
 
-// Workgroup (tile, part): 256 threads x 4 samples = samples [1024 part, 1024 (part + 1)).
-// Samples come in groups g of 256: sample 64 (4 g + k) + i, k = 0..3, i = 0..63; thread i of wave w
-// takes k = 0..3 of group 4 part + w.
+// Workgroup (tile, block): 256 samples, sample 64 (4 block + k) + i, k = 0..3, in lane i of every wave.  The WV
+// waves split the lenses: wave w takes the groups of 64 lenses w, w + WV, ..., staged privately (no barrier in
+// the loop), and the waves' FP64 sums meet in LDS in wave order.  Adding the groups' float32 sums in FP64 is exact
+// while they stay within 2^29 of each other, so the split does not show in a target.
 // Direct sum over every lens with the near ones swapped for zero-mass padding, float32 runs
 // of 16 lenses added four at a time in float32, then in FP64; writes the residual after the
 // affine base (unnormalised).
-// The four samples of a thread share one reciprocal per lens (simultaneous inversion of the
+// The four samples of a lane share one reciprocal per lens (simultaneous inversion of the
 // product of their four squared distances: a far lens is at least r_near from every sample, so no
 // product is zero).  Coordinates are staged scaled by 2^-4 (exact), which keeps that product in the
 // float32 range for lenses up to about 1e6 from the samples (6.6e4 unscaled); a lens farther than
 // that (its deflection there is below 1e-6 m) gets a zero reciprocal and is dropped.  The sums are
 // scaled back by 2^4 with the FP64 combination.  The samples' error bound stays that of the plain path (far
 // below the bfloat16 precision of the network they train).
-// GRID: the samples of a thread share their first coordinate, so x - x_l and its square are
+// GRID: the samples of a lane share their first coordinate, so x - x_l and its square are
 // computed once; every sample sees the same operations either way (the targets are
 // bit-identical), and in every launch (the layout does not depend on the number of tiles).
-__device__ __forceinline__ int sample_index(int part, int k, int tid)
-{
-    const int w = tid >> 6, lane = tid & 63;
-    return (16 * part + 4 * w + k) * 64 + lane;
-}
-
+// Bound: issue of the lens loop (28 FP32 instructions and a reciprocal per lens and four samples); which
+// kernel and how many waves, and what they measured, at launch_samples.
 constexpr float kSampleScale = 0.0625f;   // 2^-4
 // Zero-mass padding of the sample kernel, in its scaled coordinates: its squared distance (~2e18)
 // keeps every pair product finite, so the quad product overflows to a zero reciprocal and every
 // padding term is exactly 0 (never 0 x inf).
 constexpr float kSamplePad = 1.0e9f;
 
+template <bool GRID, int WV>
+__global__ void __launch_bounds__(64 * WV, WV == 16 ? 4 : 6) k_ff_samples(const FarArgs f, int blocks)
+{
+    constexpr int T = 16, G = 4, S = 4, GS = T * G;   // G runs of T lenses are added in float32, then in FP64
+    __shared__ union {
+        float4 lens[WV][GS];
+        double2 sum[WV][S][64];
+    } sm;
+    const uint32_t tile = blockIdx.x / (uint32_t)blocks, block = blockIdx.x % (uint32_t)blocks;
+    double lo[2], hi[2], c[2], hw[2];
+    int64_t i0[2];
+    int n[2];
+    tile_geom(f, tile, lo, hi, c, hw, i0, n);
+    const double rn2 = f.r_near * f.r_near;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto sample_of = [&](int k) { return 64 * (4 * (int)block + k) + lane; };
+    float px[S], py[S];   // sample positions (float32), scaled by 2^-4
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+        px[k] = (float)(c[0] + (double)f.samples[2 * sample_of(k)] * hw[0]) * kSampleScale;
+        py[k] = (float)(c[1] + (double)f.samples[2 * sample_of(k) + 1] * hw[1]) * kSampleScale;
+    }
+    double A1[S] = {}, A2[S] = {};
+    const float4 pad = make_float4(kSamplePad, kSamplePad, 0.f, 0.f);
+    // the next group's records are requested a group ahead and looked at only when they are staged
+    const int64_t groups = (f.n_lens + GS - 1) / GS;
+    const float4 *src = f.lenses + (int64_t)wave * GS + lane;
+    const int rest = (int)(f.n_lens - (groups - 1) * GS);   // lenses of the last group
+    float4 next = pad;
+    if (wave < groups - 1 || (wave == groups - 1 && lane < rest)) next = *src;
+    for (int64_t t = wave; t < groups; t += WV) {
+        const bool out = is_near(next.x, next.y, lo, hi, rn2) || (t == groups - 1 && lane >= rest);
+        sm.lens[wave][lane] = out ? pad : make_float4(next.x * kSampleScale, next.y * kSampleScale, next.z, next.w);
+        wave_sync();
+        src += WV * GS;
+        if (t + WV < groups - 1 || (t + WV == groups - 1 && lane < rest)) next = *src;
+        float m1[S], m2[S];
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+            float s1[S], s2[S];
+#pragma unroll
+            for (int j = 0; j < T; ++j) {
+                const float4 l = sm.lens[wave][h * T + j];
+                // GRID: the four samples share px[0]
+                const float dxs = px[0] - l.x, dxs2 = dxs * dxs;
+                float dx[S], dy[S], q[S];
+#pragma unroll
+                for (int k = 0; k < S; ++k) {
+                    dx[k] = GRID ? dxs : px[k] - l.x;
+                    dy[k] = py[k] - l.y;
+                    q[k] = fmaf(dy[k], dy[k], GRID ? dxs2 : dx[k] * dx[k]);
+                }
+                const float p01 = q[0] * q[1], p23 = q[2] * q[3];
+                const float g = l.z * __builtin_amdgcn_rcpf(p01 * p23);
+                const float g01 = g * p23, g23 = g * p01;
+                const float d[S] = {g01 * q[1], g01 * q[0], g23 * q[3], g23 * q[2]};
+#pragma unroll
+                for (int k = 0; k < S; ++k) {
+                    s1[k] = j == 0 ? d[k] * dx[k] : fmaf(d[k], dx[k], s1[k]);
+                    s2[k] = j == 0 ? d[k] * dy[k] : fmaf(d[k], dy[k], s2[k]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < S; ++k) {
+                m1[k] = h == 0 ? s1[k] : m1[k] + s1[k];
+                m2[k] = h == 0 ? s2[k] : m2[k] + s2[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+            A1[k] += (double)m1[k];
+            A2[k] += (double)m2[k];
+        }
+        wave_sync();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < S; ++k) sm.sum[wave][k][lane] = make_double2(A1[k], A2[k]);
+    __syncthreads();
+    if (wave >= S) return;
+    // thread (w, i) finishes the lane's sample w
+    double B1 = 0.0, B2 = 0.0;
+#pragma unroll
+    for (int w = 0; w < WV; ++w) {
+        const double2 v = sm.sum[w][wave][lane];
+        B1 += v.x;
+        B2 += v.y;
+    }
+    const int si = sample_of(wave);
+    const float x = (float)(c[0] + (double)f.samples[2 * si] * hw[0]) * kSampleScale;
+    const float y = (float)(c[1] + (double)f.samples[2 * si + 1] * hw[1]) * kSampleScale;
+    const double *h = tile_hdr(f, tile);
+    const double a01 = h[4], a02 = h[5], j11 = h[6], j12 = h[7], j22 = h[8];
+    // m (x - x_l) / r^2 of the scaled coordinates is 2^4 times the true term
+    constexpr double kBack = kRcpBiasComp / 16.0;
+    const double d1 = (double)(x * 16.0f) - c[0], d2 = (double)(y * 16.0f) - c[1];
+    const double r1 = B1 * kBack - (a01 + j11 * d1 + j12 * d2);
+    const double r2 = B2 * kBack - (a02 + j12 * d1 + j22 * d2);
+    const size_t at = ((size_t)tile * f.n_samples + si) * 2;
+    *reinterpret_cast<float2 *>(f.targets + at) = make_float2((float)r1, (float)r2);
+    if (f.debug_targets) {
+        f.debug_targets[at] = (float)r1;
+        f.debug_targets[at + 1] = (float)r2;
+    }
+}
+
+// The same sums for fits large enough to fill the GPU many times over: a workgroup takes 1024 samples, 256 per
+// wave, and its waves share each staged tile of 256 lenses, so the near tests are a quarter as many.  Samples come
+// in groups of 256: sample 64 (4 g + k) + i, k = 0..3; lane i of wave w takes k = 0..3 of group 4 part + w.
+__device__ __forceinline__ int sample_index(int part, int k, int tid)
+{
+    const int w = tid >> 6, lane = tid & 63;
+    return (16 * part + 4 * w + k) * 64 + lane;
+}
+
 template <bool GRID>
-__global__ void __launch_bounds__(256) k_ff_samples(const FarArgs f, int parts)
+__global__ void __launch_bounds__(256) k_ff_samples_tiled(const FarArgs f, int parts)
 {
     constexpr int LT = 256, T = 16, G = 4, S = 4;   // G runs of T lenses are added in float32, then in FP64
     static_assert(LT % (T * G) == 0, "tile shape");
@@ -592,13 +712,6 @@ __global__ void __launch_bounds__(256) k_ff_normalize(const FarArgs f)
 // workspace (64.5 KB per tile, read and written once per step: the working set of the tiles in
 // flight stays in L2; one 12-byte record per parameter), the bfloat16 weight copies the MFMAs read
 // and the FP32 biases in LDS.
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Sample-major staging.  Row r (one sample) of a hidden-unit array holds the 64 units as eight
 // 16-byte chunks of eight consecutive units, chunk c stored at position c ^ swz(r); a lane writes its
 // 32 units (slots 8 g .. 8 g + 7 are the units 16 g + 8 hf + e, chunk 2 g + hf) as four chunks.  The
@@ -1463,6 +1576,28 @@ hipError_t launch_affine(const FarArgs &f, int64_t count, hipStream_t s)
     return hipGetLastError();
 }
 
+// Exact samples of all tiles.  From 32768 workgroups of 256 samples on (2048 tiles of 4096 samples) the tiled kernel,
+// whose workgroup takes four times as many, is the faster one (1e5 lenses, 4096 x 4096 samples: 207.4 ms against
+// 210.3; 4096 x 1024: 55.1 against 54.1; 512 x 4096: 29.1 against 27.3).  Below, so many waves share the lenses that
+// the GPU is full: sixteen up to 256 workgroups (9 x 1024 samples: 1.1 ms, eight waves 1.2, four 2.2, tiled 8.4),
+// eight up to 16384 (512 x 4096: 26.8 ms, four waves 27.4; 35 x 1024 3.1, 3.3, sixteen 3.3).
+template <bool GRID>
+hipError_t launch_samples(const FarArgs &f, hipStream_t s)
+{
+    const int blocks = f.n_samples / 256;
+    const int64_t wgs = f.n_tiles * blocks;
+    const dim3 g((unsigned)wgs);
+    if (wgs >= 32768)
+        hipLaunchKernelGGL((k_ff_samples_tiled<GRID>), dim3((unsigned)(wgs / 4)), dim3(256), 0, s, f, blocks / 4);
+    else if (wgs > 16384)
+        hipLaunchKernelGGL((k_ff_samples<GRID, 4>), g, dim3(64 * 4), 0, s, f, blocks);
+    else if (wgs > 256)
+        hipLaunchKernelGGL((k_ff_samples<GRID, 8>), g, dim3(64 * 8), 0, s, f, blocks);
+    else
+        hipLaunchKernelGGL((k_ff_samples<GRID, 16>), g, dim3(64 * 16), 0, s, f, blocks);
+    return hipGetLastError();
+}
+
 hipError_t launch_ff_fit(const FarArgs &f, uint64_t hash, hipStream_t s)
 {
     const uint32_t nt = (uint32_t)f.n_tiles;
@@ -1474,12 +1609,7 @@ hipError_t launch_ff_fit(const FarArgs &f, uint64_t hash, hipStream_t s)
         hipSuccess)
         return e;
     if ((e = launch_affine(f, nt, s)) != hipSuccess) return e;
-    const int parts = f.n_samples / 1024;
-    if (f.grid_samples)
-        hipLaunchKernelGGL(k_ff_samples<true>, dim3(nt * (uint32_t)parts), dim3(256), 0, s, f, parts);
-    else
-        hipLaunchKernelGGL(k_ff_samples<false>, dim3(nt * (uint32_t)parts), dim3(256), 0, s, f, parts);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = f.grid_samples ? launch_samples<true>(f, s) : launch_samples<false>(f, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_ff_normalize, dim3(nt), dim3(256), 0, s, f);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (f.steps > 0) {
