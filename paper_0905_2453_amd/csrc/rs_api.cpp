@@ -279,7 +279,7 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     // Work items: a tile of rays, or of one-column blocks as many as make up about 2048 lenses' work (an item
     // taken from the counter costs about 12 ns), and at least so many that their number stays below that of
     // the tiles where it could pass 2^31.
-    uint64_t items = 0, taken = 0, inter = 0, tiles = 0;
+    uint64_t items = 0, taken = 0, inter = 0, tiles = 0, blocks = 0;
     for (int32_t k = 0; k < n_jobs; ++k) tiles += (uint64_t)tile_count(&jobs[k], t);
     if (tiles >= (uint64_t(1) << 31)) return fail(RS_ERANGE, "more than 2^31 ray tiles in one batch");
     const int64_t least = tiles >= (uint64_t(1) << 29) ? rs::kWaves : 1;
@@ -301,6 +301,7 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
         if (t.K1 == 1) {
             const int64_t q = std::max(least, std::min<int64_t>(16, 2048 / std::max<int64_t>(job->n_lens, 1)));
             args[k].per_item = (uint32_t)q;
+            blocks += args[k].n_blocks;
             nt = ((int64_t)args[k].n_blocks + q - 1) / q;
             rays_per_item = 256ull * (uint64_t)q;
         }
@@ -317,7 +318,7 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return dev_fail(e, "device query");
-    if (t.K1 == 1) pb.waves = rs::split_batched_waves(n_jobs > 0 ? jobs[order[0]].n_lens : 0);
+    if (t.K1 == 1) pb.waves = rs::split_batched_waves(blocks, n_jobs > 0 ? jobs[order[0]].n_lens : 0);
     const int occ = t.K1 == 1 ? rs::split_batched_occupancy(t.run(), t.LT, pb.waves)
                               : rs::batched_occupancy(t.K1, t.K2, t.run(), t.LT);
     if (occ <= 0) return fail(RS_EINTERNAL, "no occupancy for the batched kernel");
