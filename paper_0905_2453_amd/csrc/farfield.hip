@@ -712,6 +712,11 @@ __global__ void __launch_bounds__(256) k_ff_normalize(const FarArgs f)
 // workspace (64.5 KB per tile, read and written once per step: the working set of the tiles in
 // flight stays in L2; one 12-byte record per parameter), the bfloat16 weight copies the MFMAs read
 // and the FP32 biases in LDS.
+// What bounds it is vector-instruction issue: per round a wave issues 650 plain and 136
+// transcendental instructions, 72 % of its SIMD's cycles with the other wave's, MFMAs 14 %, LDS 38 %.
+// Hence the address arithmetic kept to one offset per operand, and the update spread evenly: 11
+// parameters a lane at most, the columns added up by the lane that needs them (17 a lane, with a
+// cross-lane exchange first: 55.1 ms for 500 steps of 2048 tiles, so 53.0).
 // Sample-major staging.  Row r (one sample) of a hidden-unit array holds the 64 units as eight
 // 16-byte chunks of eight consecutive units, chunk c stored at position c ^ swz(r); a lane writes its
 // 32 units (slots 8 g .. 8 g + 7 are the units 16 g + 8 hf + e, chunk 2 g + hf) as four chunks.  The
@@ -787,20 +792,31 @@ struct AdamState {
 
 // Per-step factors of the optimiser, in FP64 and rounded once: the cosine-decayed learning rate
 // lr (1 + cos(pi (t - 1) / S)) / 2 and the bias corrections 1 / (1 - beta^t) of step t (1-based).
+// One workgroup, 256 steps at a time: the powers are a chain of products in one thread, the rest of
+// each step is a thread's own (with the quotients in the chain, 500 steps took 212 us, so 37).
 __global__ void __launch_bounds__(256) k_adam_schedule(const FarArgs f)
 {
-    for (int t = (int)threadIdx.x + 1; t <= f.steps; t += 256) {
-        f.sched[4 * (t - 1)] = (float)((double)f.lr * 0.5 * (1.0 + cos(3.14159265358979323846 * (t - 1) / f.steps)));
-        f.sched[4 * (t - 1) + 3] = 0.f;
-    }
-    if (threadIdx.x == 0) {
-        double b1t = 1.0, b2t = 1.0;
-        for (int t = 1; t <= f.steps; ++t) {
-            b1t *= 0.9;
-            b2t *= 0.999;
-            f.sched[4 * (t - 1) + 1] = (float)(1.0 / (1.0 - b1t));
-            f.sched[4 * (t - 1) + 2] = (float)(1.0 / (1.0 - b2t));
+    __shared__ double pw[2][256];
+    double b1t = 1.0, b2t = 1.0;
+    for (int t0 = 0; t0 < f.steps; t0 += 256) {
+        const int n = min(256, f.steps - t0), i = threadIdx.x;
+        if (i == 0) {
+            for (int k = 0; k < n; ++k) {
+                b1t *= 0.9;
+                b2t *= 0.999;
+                pw[0][k] = b1t;
+                pw[1][k] = b2t;
+            }
         }
+        __syncthreads();
+        if (i < n) {
+            float *o = f.sched + 4 * (int64_t)(t0 + i);
+            o[0] = (float)((double)f.lr * 0.5 * (1.0 + cos(3.14159265358979323846 * (t0 + i) / f.steps)));
+            o[1] = (float)(1.0 / (1.0 - pw[0][i]));
+            o[2] = (float)(1.0 / (1.0 - pw[1][i]));
+            o[3] = 0.f;
+        }
+        __syncthreads();
     }
 }
 
@@ -865,28 +881,50 @@ __global__ void __launch_bounds__(kTrainThreads) k_mlp_train(const FarArgs f)
         f32x4 g2[2][2] = {}, g1 = {}, gb1v = {}, gb2v = {};
         f32x4 w3m[4] = {}, gb3m = {};   // dW3 by unit block and b3: column lane % 16 < 4 holds d3 term n
         // owned weight-gradient blocks contracted over this round's samples, in wave order (the
-        // operand addresses are recomputed here from laundered indices, not kept across the round)
+        // operand addresses are recomputed here from laundered indices, not kept across the round:
+        // one per block and row half, the waves' arrays at constant distances from it)
         auto contract = [&]() __attribute__((always_inline)) {
             int cl = lane, cw = wave;
             asm volatile("" : "+v"(cl), "+v"(cw));
-            const int r2 = (cw & 3) >> 1, c2 = cw & 1, tt = cw & 3, vv = 4 * (cw >> 2);
+            const int r2 = (cw & 3) >> 1, c2 = cw & 1, tt = cw & 3;
             const TrLane tl = tr_lane(cl);
+            const uint8_t *rows = reinterpret_cast<const uint8_t *>(sstage) + 2 * kStageWords * 4 * (cw >> 2) + tl.row0;
+            auto chunk = [&](int b) __attribute__((always_inline)) { return ((2 * b) ^ tl.y0) << 4; };
+            const int ca[2] = {chunk(2 * r2 + c2), chunk(2 * r2 + (c2 ^ 1))};
+            const int cb[2] = {chunk(2 * c2), chunk(2 * c2 + 1)}, c1 = chunk(tt);
+            const uint8_t *pa[2][2], *pb[2][2], *p1[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    pa[i][h] = rows + (ca[i] ^ (h << 4));
+                    pb[i][h] = rows + (cb[i] ^ (h << 4));
+                }
+                p1[h] = rows + (c1 ^ (h << 4));
+            }
+            const uint16_t *phi = sphi[4 * (cw >> 2)];
+            constexpr int kArr = 2 * kTrainWaves * kStageWords;   // bytes from one array to the next
+            auto operand = [](const uint8_t *const(&p)[2], int off) __attribute__((always_inline)) {
+                const bf16x4 v0 = lds_tr4(p[0] + off), v1 = lds_tr4(p[1] + off + 512);
+                return __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+            };
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
+                const int at = 2 * kStageWords * v;
                 bf16x8 a[2], b[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    a[i] = tr_units(stg(0, vv + v), 2 * r2 + i, tl);
-                    b[i] = tr_units(stg(1, vv + v), 2 * c2 + i, tl);
+                    a[i] = operand(pa[i], at);
+                    b[i] = operand(pb[i], at + kArr);
                 }
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
                     for (int j = 0; j < 2; ++j)
                         g2[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], g2[i][j], 0, 0, 0);
-                gb2v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c2 ? a[1] : a[0], ones, gb2v, 0, 0, 0);
-                const bf16x8 a1 = tr_units(stg(2, vv + v), tt, tl);
-                const bf16x8 b1 = tr_phi(sphi[vv + v], cl);
+                gb2v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], ones, gb2v, 0, 0, 0);
+                const bf16x8 a1 = operand(p1, at + 2 * kArr);
+                const bf16x8 b1 = tr_phi(phi + 16 * 32 * v, cl);
                 g1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, g1, 0, 0, 0);
                 gb1v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, ones, gb1v, 0, 0, 0);
             }
@@ -903,6 +941,11 @@ __global__ void __launch_bounds__(kTrainThreads) k_mlp_train(const FarArgs f)
             uint32_t phi4[4];
             features8(u, phi4);
             stage_phi(sphi[wave], col, hf, phi4);
+            // Of a SIMD's two waves the older one is served first, waits at the barrier below for a third
+            // of the round and leaves the other alone there.  Waves 4-7 go first through the forward
+            // pass: waves 0-3, first by age from then on, run theirs against the others' backward pass
+            // (500 steps of 2048 tiles: 53.0 ms without, 50.7 with).
+            if (__builtin_amdgcn_readfirstlane(wave) >= kTrainWaves / 2) __builtin_amdgcn_s_setprio(1);
             // forward: layer 1, layer 2 (each staged as soon as it is computed), layer 3
             float d1[32], d2[32];
             uint32_t h1[16], h2[16];
@@ -913,6 +956,7 @@ __global__ void __launch_bounds__(kTrainThreads) k_mlp_train(const FarArgs f)
             stage_row(h2s, col, hf, h2);
             float o0, o1;
             layer3_dot(Wbf, sbias, h2, hf, o0, o1);
+            __builtin_amdgcn_s_setprio(0);
             const float d30 = (o0 - t0) * inv_b, d31 = (o1 - t1) * inv_b;
             // dz2 = bf16(dh2 * silu'(z2)), dh2 = W3^T d3 as one 32x32x16 MFMA per output tile: d3 enters
             // as two bfloat16 terms hi + lo (equal to d3 within 2^-18 of it, far below the bfloat16
@@ -987,60 +1031,54 @@ __global__ void __launch_bounds__(kTrainThreads) k_mlp_train(const FarArgs f)
         // (a few integer operations) instead of being kept, or spilled, across the rounds.
         int ln = lane, wv = wave;
         asm volatile("" : "+v"(ln), "+v"(wv));
-        // The lane's parameters: slots 0-7 dW2 (tiles (i, w / 4) of its block), 8-11 dW1 (waves 0-3),
-        // 12-15 the biases and layer-3 weights of unit 8 w + lane (lanes 0-7), slot 12 b3 (wave 0,
-        // lanes 8 and 9); -1 = none.
-        const int m16 = ln & 15, q4 = ln >> 4, own = wv >> 2;
-        constexpr int kSlots = 16;
-        int pid[kSlots];
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            pid[k] = kOffW2 + 64 * (32 * ((wv & 3) >> 1) + 16 * (k >> 2) + 4 * q4 + (k & 3)) + 32 * (wv & 1) + 16 * own +
-                     m16;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) pid[8 + r] = wv < 4 ? kOffW1 + 16 * (16 * (wv & 3) + 4 * q4 + r) + m16 : -1;
-        {
-            const int un = 8 * wv + ln;
-            pid[12] = ln < 8 ? kOffB1 + un : (wv == 0 && ln < 10 ? kOffB3 + ln - 8 : -1);
-            pid[13] = ln < 8 ? kOffB2 + un : -1;
-            pid[14] = ln < 8 ? kOffW3 + un : -1;
-            pid[15] = ln < 8 ? kOffW3 + 64 + un : -1;
-        }
+        // The lane's parameters: slots 4 i + r dW2, rows 32 R + 16 (i ^ C) + 4 q4 + r of column 32 C +
+        // 16 (w / 4) + m16 (the gradient tile (i, w / 4) of its block); 8-9 dW1, rows 16 (w % 4) + 4 q4
+        // + 2 (w / 4) + 0, 1 of feature m16; slot 10, of lanes 0-31, b1, b2 and the two layer-3 weights
+        // of the units 8 w + lane % 8, and b3 in lanes 32 and 33 of wave 0.  Each slot's state is at a
+        // 32-bit offset from the tile's, its neighbours' at constant distances.
+        const int m16 = ln & 15, q4 = (ln >> 4) & 3, own = (wv >> 2) & 1, R = (wv & 3) >> 1, C = wv & 1;
+        constexpr int kSlots = 11;
+        const int col2 = 32 * C + 16 * own + m16, rowb = 32 * R + 4 * q4, row1 = 16 * (wv & 3) + 4 * q4 + 2 * own;
+        const int row2[2] = {rowb + 16 * C, rowb + 16 * (C ^ 1)};
+        const int kind = ln >> 3, un = 8 * wv + (ln & 7);
+        const bool last = ln < 32 || (wv == 0 && ln < 34);
+        const int plast = ln < 32 ? (kind == 0 ? kOffB1 : kind == 1 ? kOffB2 : kOffW3 + 64 * (kind - 2)) + un
+                                  : (last ? kOffB3 + ln - 32 : 0);
+        uint8_t *obytes = reinterpret_cast<uint8_t *>(ost);
+        auto rec = [&](int p, int ahead) __attribute__((always_inline)) {
+            return reinterpret_cast<AdamState *>(obytes + (uint32_t)((uint32_t)sizeof(AdamState) * (uint32_t)p)) + ahead;
+        };
+        const int p2[2] = {kOffW2 + 64 * row2[0] + col2, kOffW2 + 64 * row2[1] + col2}, p1 = kOffW1 + 16 * row1 + m16;
         // the optimiser state of every slot is requested before the last round's contraction and the
         // exchange, so its global round trip overlaps them
         AdamState st[kSlots];
 #pragma unroll
-        for (int k = 0; k < kSlots; ++k) st[k] = ost[pid[k] < 0 ? 0u : (uint32_t)pid[k]];
+        for (int k = 0; k < 8; ++k) st[k] = *rec(p2[k >> 2], 64 * (k & 3));
+#pragma unroll
+        for (int r = 0; r < 2; ++r) st[8 + r] = *rec(p1, 16 * r);
+        st[10] = *rec(plast, 0);
         contract();
-        // dW3 and b3 of output o = column o (hi term) + column o + 2 (lo term), held two lanes apart
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) w3m[b][r] += __shfl_down(w3m[b][r], 2);
-        const float gb3 = gb3m[0] + __shfl_down(gb3m[0], 2);
         __syncthreads();   // the last round's readers are done: the staging area takes the partial sums
-        float *xg1 = reinterpret_cast<float *>(sstage);    // [wave / 4][unit]: b1 partials
-        float *xg2 = xg1 + 2 * 64;                         // [wave / 4][unit]: b2 partials
-        float *xw3 = xg2 + 2 * 64;                         // [wave][o][unit]: dW3 partials
-        float *x3 = xw3 + kTrainWaves * 2 * 64;            // [wave][o]: b3 partials
-        float *x1 = x3 + kTrainWaves * 2;                  // [wave - 4][lane][4]: dW1 partials of waves 4-7
-        float *x2 = x1 + 4 * 64 * 4;                       // [wave][lane][8]: dW2 tiles the wave does not own
-        if ((ln & 15) == 0) {
-            *reinterpret_cast<f32x4 *>(xg1 + own * 64 + 16 * (wv & 3) + 4 * (ln >> 4)) = gb1v;
-            *reinterpret_cast<f32x4 *>(xg2 + own * 64 + 32 * ((wv & 3) >> 1) + 16 * (wv & 1) + 4 * (ln >> 4)) = gb2v;
+        // Rows of kRow floats: [w / 4]: b1 and b2 partials; then [wave]: the four d3 columns of dW3
+        // (hi and lo term of output 0 and 1: columns o and o + 2) by unit, and of b3.
+        constexpr int kRow = 4 * 64 + 4;
+        float *xg = reinterpret_cast<float *>(sstage);
+        float *xw = xg + 2 * kRow;
+        float *x1 = xw + kTrainWaves * kRow;               // [wave][lane][2]: dW1 rows the wave does not own
+        float *x2 = x1 + kTrainThreads * 2;                // [wave][lane][8]: dW2 tiles the wave does not own
+        if (m16 == 0) {
+            *reinterpret_cast<f32x4 *>(xg + own * kRow + 16 * (wv & 3) + 4 * q4) = gb1v;
+            *reinterpret_cast<f32x4 *>(xg + own * kRow + 64 + 32 * R + 16 * C + 4 * q4) = gb2v;
         }
-        if ((ln & 15) < 2) {
-            // lane (G, o): units 16 b + 4 G + r
+        if (m16 < 4) {
+            // lane (q4, column): units 16 b + 4 q4 + r
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
-                *reinterpret_cast<f32x4 *>(xw3 + (wv * 2 + (ln & 15)) * 64 + 16 * b + 4 * (ln >> 4)) = w3m[b];
-        }
-        if (ln < 2) x3[wv * 2 + ln] = gb3;
-        if (wv >= 4) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) x1[((wv - 4) * 64 + ln) * 4 + r] = g1[r];
+            for (int b = 0; b < 4; ++b) *reinterpret_cast<f32x4 *>(xw + wv * kRow + m16 * 64 + 16 * b + 4 * q4) = w3m[b];
+            if (q4 == 0) xw[wv * kRow + 256 + m16] = gb3m[0];
         }
         {
+            using f32x2 = float __attribute__((ext_vector_type(2)));
+            *reinterpret_cast<f32x2 *>(x1 + (wv * 64 + ln) * 2) = own ? f32x2{g1[0], g1[1]} : f32x2{g1[2], g1[3]};
             // the partner wave (the other sample half of the same block) owns tiles (i, 1 - w / 4)
             f32x4 *o = reinterpret_cast<f32x4 *>(x2 + (wv * 64 + ln) * 8);
             o[0] = own ? g2[0][0] : g2[0][1];
@@ -1049,38 +1087,29 @@ __global__ void __launch_bounds__(kTrainThreads) k_mlp_train(const FarArgs f)
         __syncthreads();
         float gr[kSlots];
         {
-            const f32x4 *o = reinterpret_cast<const f32x4 *>(x2 + ((wv ^ 4) * 64 + ln) * 8);
-            const f32x4 p0 = o[0], p1 = o[1];
+            const int other = (wv ^ 4) * 64 + ln;
+            const f32x4 *o = reinterpret_cast<const f32x4 *>(x2 + other * 8);
+            const f32x4 o0 = o[0], o1 = o[1];
             const f32x4 m0 = own ? g2[0][1] : g2[0][0], m1 = own ? g2[1][1] : g2[1][0];
-            // half 0 (waves 0-3) first
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                gr[r] = own ? p0[r] + m0[r] : m0[r] + p0[r];
-                gr[4 + r] = own ? p1[r] + m1[r] : m1[r] + p1[r];
+                gr[r] = m0[r] + o0[r];
+                gr[4 + r] = m1[r] + o1[r];
             }
+#pragma unroll
+            for (int r = 0; r < 2; ++r) gr[8 + r] = (own ? g1[2 + r] : g1[r]) + x1[other * 2 + r];
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) gr[8 + r] = wv < 4 ? g1[r] + x1[(wv * 64 + ln) * 4 + r] : 0.f;
-        if (ln < 8) {
-            const int un = 8 * wv + ln;
-            gr[12] = xg1[un] + xg1[64 + un];
-            gr[13] = xg2[un] + xg2[64 + un];
-            float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-            for (int v = 0; v < kTrainWaves; ++v) {
-                s0 += xw3[(v * 2 + 0) * 64 + un];
-                s1 += xw3[(v * 2 + 1) * 64 + un];
-            }
-            gr[14] = s0;
-            gr[15] = s1;
+        if (ln < 16) {
+            const float *x = xg + 64 * kind + un;
+            gr[10] = x[0] + x[kRow];
         } else {
+            // columns o and o + 2 of each wave, waves in order (the other lanes' sums are not used)
+            const int o = ln < 32 ? 64 * (kind - 2) + un : 256 + (ln & 1);
+            const int lo = ln < 32 ? 128 : 2;
             float g = 0.f;
-            if (wv == 0 && ln < 10) {
 #pragma unroll
-                for (int v = 0; v < kTrainWaves; ++v) g += x3[v * 2 + ln - 8];
-            }
-            gr[12] = g;
-            gr[13] = gr[14] = gr[15] = 0.f;
+            for (int v = 0; v < kTrainWaves; ++v) g += xw[v * kRow + o] + xw[v * kRow + o + lo];
+            gr[10] = g;
         }
         // Adam with bias correction and a cosine-decayed learning rate (the step's factors from the
         // schedule table); square root and quotient by the hardware instructions (1 ulp, far below
@@ -1096,59 +1125,36 @@ __global__ void __launch_bounds__(kTrainThreads) k_mlp_train(const FarArgs f)
             return AdamState{s0.w - lr_t * (m * ibc1) * __builtin_amdgcn_rcpf(d), m, v};
         };
         {
-            // dW2 slots 4 i + r: row 32 R + 16 i + 4 q4 + r, column 32 C + 16 (w / 4) + m16; their LDS
-            // positions in the swizzled W2 and W2T (see m64) follow from that structure
-            const int q4b = q4 & 3, R = (wv & 3) >> 1;
-            const int col2 = 32 * (wv & 1) + 16 * own + m16, rowb = 32 * R + 4 * q4b;
-            const int cx = (col2 >> 3) ^ ((q4b & 2) << 1);
-            const int y = (4 * R + (q4b >> 1)) ^ wsw(col2);
+            // dW2: the LDS positions in the swizzled W2 and W2T (see m64) follow from the structure of
+            // the rows
+            const int cx = (col2 >> 3) ^ ((q4 & 2) << 1);
+            const int y = (4 * R + (q4 >> 1) + 2 * C) ^ wsw(col2);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const int i = k >> 2, r = k & 3;
-                const int row = rowb + 16 * i + r;
-                const int p = kOffW2 + 64 * row + col2;
                 const AdamState s1 = adam(st[k], gr[k]);
-                if (dbg) dg[p] = gr[k];
-                ost[p] = s1;
+                if (dbg) dg[p2[i] + 64 * r] = gr[k];
+                *rec(p2[i], 64 * r) = s1;
                 const uint16_t b = to_bf16(s1.w);
-                Wbf[kOffW2 + 64 * row + (((cx ^ r) << 3) | (col2 & 7))] = b;
-                W2T[col2 * 64 + (((y ^ (2 * i)) << 3) | (4 * (q4b & 1) + r))] = b;
+                Wbf[kOffW2 + 64 * (row2[i] + r) + (((cx ^ r) << 3) | (col2 & 7))] = b;
+                W2T[col2 * 64 + (((y ^ (2 * i)) << 3) | (4 * (q4 & 1) + r))] = b;
             }
         }
-        if (wv < 4) {
-            // dW1 slots: rows 16 w + 4 q4 + r, feature m16
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int p = kOffW1 + 16 * (16 * (wv & 3) + 4 * q4 + r) + m16;
-                const AdamState s1 = adam(st[8 + r], gr[8 + r]);
-                if (dbg) dg[p] = gr[8 + r];
-                ost[p] = s1;
-                Wbf[p] = to_bf16(s1.w);
-            }
+        for (int r = 0; r < 2; ++r) {
+            const AdamState s1 = adam(st[8 + r], gr[8 + r]);
+            if (dbg) dg[p1 + 16 * r] = gr[8 + r];
+            *rec(p1, 16 * r) = s1;
+            Wbf[p1 + 16 * r] = to_bf16(s1.w);
         }
-        if (ln < 8) {
-            // b1, b2 and the two layer-3 weights of unit 8 w + lane
-            const int un = 8 * wv + ln;
-            const int ps[4] = {kOffB1 + un, kOffB2 + un, kOffW3 + un, kOffW3 + 64 + un};
-            uint32_t w3pair = 0u;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const AdamState s1 = adam(st[12 + k], gr[12 + k]);
-                if (dbg) dg[ps[k]] = gr[12 + k];
-                ost[ps[k]] = s1;
-                const uint16_t b = to_bf16(s1.w);
-                Wbf[ps[k]] = b;
-                if (k < 2) sbias[64 * k + un] = s1.w;
-                else w3pair |= (uint32_t)b << (16 * (k - 2));
-            }
-            sW3p[un] = w3pair;
-        } else if (wv == 0 && ln < 10) {
-            const int p = kOffB3 + ln - 8;
-            const AdamState s1 = adam(st[12], gr[12]);
-            if (dbg) dg[p] = gr[12];
-            ost[p] = s1;
-            Wbf[p] = to_bf16(s1.w);
-            sbias[128 + ln - 8] = s1.w;
+        if (last) {
+            const AdamState s1 = adam(st[10], gr[10]);
+            if (dbg) dg[plast] = gr[10];
+            *rec(plast, 0) = s1;
+            const uint16_t b = to_bf16(s1.w);
+            Wbf[plast] = b;
+            if (ln >= 16 && ln < 32) reinterpret_cast<uint16_t *>(sW3p)[2 * un + (kind & 1)] = b;
+            else sbias[ln < 16 ? 64 * kind + un : 128 + (ln & 1)] = s1.w;
         }
     }
     __syncthreads();
