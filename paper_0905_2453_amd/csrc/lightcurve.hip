@@ -11,7 +11,8 @@ namespace rs {
 namespace {
 
 constexpr int kLcWaves = 4;
-constexpr int kLcAxis = 128;   // support bounding-box side staged in LDS per wave
+constexpr int kLcAxis = 128;   // support bounding-box side staged in LDS per wave of a point
+constexpr int kLcAhead = 4;    // pixels requested at once when there are few points
 
 __device__ inline double wave_sum(double v)
 {
@@ -19,18 +20,29 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-// One wave per track point.  Lane l takes the bounding-box pixels e = l, l + 64, ... (row-major)
-// and the wave then reduces in a fixed butterfly order, so a result depends only on its inputs.
-// A Gaussian weight is separable, exp(-(d1^2 + d2^2) / 2 s^2) = g(d1) g(d2): each wave stages the
-// squared offsets and the one-axis factors of its box's columns and rows in LDS, leaving one
+// One wave per track point (SPLIT 1), or one workgroup (SPLIT kLcWaves).  The point's lane l takes the
+// bounding-box pixels e = l, l + 64 SPLIT, ... (row-major); each wave reduces in a fixed butterfly order and
+// a workgroup adds its waves' sums in order, so a result depends only on its inputs.
+// A Gaussian weight is separable, exp(-(d1^2 + d2^2) / 2 s^2) = g(d1) g(d2): the squared offsets and the
+// one-axis factors of the box's columns and rows are staged in LDS, leaving one
 // product per pixel.  The inclusion test d1^2 + d2^2 <= R^2 uses the same FP64 expressions as the
 // plain definition.  Boxes wider than the staging area take the per-pixel path.
+//
+// Many points: issue; a pixel outside the support is not read (AHEAD 1).  Few points leave a wave or two per
+// SIMD and nothing to cover the latency of a pixel's load: AHEAD pixels are requested at once, those outside the
+// support with weight zero (2107 points, box 1764: 10.2 us, 8.8 with four ahead), and where there are
+// not even waves enough, a workgroup shares a point (300 points, box 1764: 8.5 us, 4.4; box 14884: 47.1, 10.1).
+// A point of a workgroup also has four times the staging area: 2107 points, box 58564: 391 us, 90.2 staged.
+template <int SPLIT, int AHEAD>
 __global__ void __launch_bounds__(64 * kLcWaves) k_light_curve(const LightArgs a)
 {
-    __shared__ double2 s_col[kLcWaves][kLcAxis];   // (d1^2, g(d1)) per box column
-    __shared__ double2 s_row[kLcWaves][kLcAxis];   // (d2^2, g(d2)) per box row
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t gp = (int64_t)blockIdx.x * kLcWaves + wv;
+    constexpr int kPoints = kLcWaves / SPLIT, kLanes = 64 * SPLIT;   // points of a workgroup, lanes of a point
+    static_assert(SPLIT == 1 || SPLIT == kLcWaves, "a point belongs to a wave or to the workgroup");
+    __shared__ double2 s_col[kPoints][kLcAxis * SPLIT];   // (d1^2, g(d1)) per box column
+    __shared__ double2 s_row[kPoints][kLcAxis * SPLIT];   // (d2^2, g(d2)) per box row
+    __shared__ double s_sum[kLcWaves][2];
+    const int lane = threadIdx.x % kLanes, wv = threadIdx.x / kLanes;
+    const int64_t gp = (int64_t)blockIdx.x * kPoints + wv;
     const bool active = gp < (int64_t)a.n_tracks * a.n_points;
     int64_t tr = 0;
     int k = 0;
@@ -61,14 +73,14 @@ __global__ void __launch_bounds__(64 * kLcWaves) k_light_curve(const LightArgs a
     const int p2lo = (int)fmax(0.0, fmin(q2lo, (double)a.n[1]));
     const int p2hi = (int)fmax(-1.0, fmin(q2hi, (double)a.n[1] - 1));
     const int nx = active ? p1hi - p1lo + 1 : 0, ny = active ? p2hi - p2lo + 1 : 0;
-    const bool staged = nx <= kLcAxis && ny <= kLcAxis;
+    const bool staged = nx <= kLcAxis * SPLIT && ny <= kLcAxis * SPLIT;
     if (staged) {
-        for (int c = lane; c < nx; c += 64) {
+        for (int c = lane; c < nx; c += kLanes) {
             const double d = (a.lo[0] + ((double)(p1lo + c) + 0.5) * a.w[0]) - ys1;
             const double d2 = d * d;
             s_col[wv][c] = make_double2(d2, gauss ? exp(-d2 * inv2s2) : 1.0);
         }
-        for (int r = lane; r < ny; r += 64) {
+        for (int r = lane; r < ny; r += kLanes) {
             const double d = (a.lo[1] + ((double)(p2lo + r) + 0.5) * a.w[1]) - ys2;
             const double d2 = d * d;
             s_row[wv][r] = make_double2(d2, gauss ? exp(-d2 * inv2s2) : 1.0);
@@ -79,33 +91,58 @@ __global__ void __launch_bounds__(64 * kLcWaves) k_light_curve(const LightArgs a
     if (nx > 0 && ny > 0) {
         if (staged) {
             const int total = nx * ny;
-            // e = dr * nx + dc, advanced by 64 without a division per pixel
+            // e = dr * nx + dc, advanced by kLanes without a division per pixel
             int dr = lane / nx, dc = lane - (lane / nx) * nx;
-            const int sr = 64 / nx, sc = 64 - (64 / nx) * nx;
-            const uint32_t *base = a.counts + (int64_t)k * a.frame_stride + (int64_t)p2lo * a.n[0] + p1lo;
-            for (int e = lane; e < total; e += 64) {
-                const double2 cx = s_col[wv][dc], ry = s_row[wv][dr];
-                if (cx.x + ry.x <= rs2) {
-                    const double n = (double)base[(int64_t)dr * a.n[0] + dc];
-                    if (gauss) {
-                        const double wgt = cx.y * ry.y;
-                        num += wgt * n;
-                        den += wgt;
-                    } else {
-                        num += n;
-                        den += 1.0;
-                    }
-                }
+            const int sr = kLanes / nx, sc = kLanes - (kLanes / nx) * nx;
+            const int64_t n0 = a.n[0];
+            const uint32_t *base = a.counts + (int64_t)k * a.frame_stride + (int64_t)p2lo * n0 + p1lo;
+            auto advance = [&]() {
                 dc += sc;
                 dr += sr;
                 if (dc >= nx) {
                     dc -= nx;
                     ++dr;
                 }
+            };
+            if constexpr (AHEAD == 1) {
+                for (int e = lane; e < total; e += kLanes) {
+                    const double2 cx = s_col[wv][dc], ry = s_row[wv][dr];
+                    if (cx.x + ry.x <= rs2) {
+                        const double n = (double)base[(int64_t)dr * n0 + dc];
+                        if (gauss) {
+                            const double wgt = cx.y * ry.y;
+                            num += wgt * n;
+                            den += wgt;
+                        } else {
+                            num += n;
+                            den += 1.0;
+                        }
+                    }
+                    advance();
+                }
+            } else {
+                for (int e = lane; e < total; e += kLanes * AHEAD) {
+                    double wgt[AHEAD];
+                    uint32_t n[AHEAD];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        const bool box = e + kLanes * u < total;
+                        const int c = box ? dc : 0, r = box ? dr : 0;
+                        const double2 cx = s_col[wv][c], ry = s_row[wv][r];
+                        n[u] = base[(int64_t)r * n0 + c];
+                        wgt[u] = box && cx.x + ry.x <= rs2 ? (gauss ? cx.y * ry.y : 1.0) : 0.0;
+                        advance();
+                    }
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        num += wgt[u] * (double)n[u];
+                        den += wgt[u];
+                    }
+                }
             }
         } else {
             const int64_t total = (int64_t)nx * ny;
-            for (int64_t e = lane; e < total; e += 64) {
+            for (int64_t e = lane; e < total; e += kLanes) {
                 const int r = (int)(e / nx);
                 const int p1 = p1lo + (int)(e - (int64_t)r * nx), p2 = p2lo + r;
                 const double d1 = (a.lo[0] + ((double)p1 + 0.5) * a.w[0]) - ys1;
@@ -121,6 +158,18 @@ __global__ void __launch_bounds__(64 * kLcWaves) k_light_curve(const LightArgs a
     }
     num = wave_sum(num);
     den = wave_sum(den);
+    if constexpr (SPLIT > 1) {
+        if ((threadIdx.x & 63) == 0) {
+            s_sum[threadIdx.x >> 6][0] = num;
+            s_sum[threadIdx.x >> 6][1] = den;
+        }
+        __syncthreads();
+        num = den = 0.0;
+        for (int w = 0; w < kLcWaves; ++w) {
+            num += s_sum[w][0];
+            den += s_sum[w][1];
+        }
+    }
     if (active && lane == 0) {
         const double mu = den > 0.0 ? num / (den * a.n_av) : __builtin_nan("");
         if (a.mu) a.mu[gp] = mu;
@@ -263,23 +312,37 @@ hipError_t launch_light_curve(const LightArgs &a, hipStream_t s)
     const int64_t pts = (int64_t)a.n_tracks * a.n_points;
     if (pts <= 0) return hipSuccess;
     // the support box spans at most this many pixels per axis
-    const double bx = std::ceil(2.0 * a.support * a.inv_w[0]) + 2.0, by = std::ceil(2.0 * a.support * a.inv_w[1]) + 2.0;
-    // Which layout is faster, from what both measured over 600 to 1e6 points and boxes of 15 to 1e5 pixels: a wave
-    // takes 0.62 ns a point and 0.54 ps a pixel of its box (1.6 ps where the box is not staged), all waves together;
-    // lanes take 0.21 ps a pixel, but never less than 13 us and 43 ns a pixel, one lane's walk.  38400 points: box
-    // 234 lanes 24 us, waves 35; 1279 76, 60; 27836 981, 1788.  1e6 points: box 7211 lanes 1.66 ms, waves 4.79.
-    const double box = bx * by, np = (double)pts;
-    const double t_wave = np * (0.62 + (bx <= kLcAxis && by <= kLcAxis ? 0.54e-3 : 1.6e-3) * box);
+    const double bx = std::min(std::ceil(2.0 * a.support * a.inv_w[0]) + 2.0, (double)a.n[0]);
+    const double by = std::min(std::ceil(2.0 * a.support * a.inv_w[1]) + 2.0, (double)a.n[1]);
+    // Which layout is faster, from what each measured over 50 to 1e6 points and boxes of 15 to 6e4 pixels: the
+    // time of one point on an idle GPU and the time that a point of very many adds, combined as a root of
+    // squares.  Waves take 0.62 ns a point and 0.58 ps a pixel of its box, but 3.2 us and 2.9 ns a pixel one by
+    // one; with pixels requested ahead 0.75, 0.63, 3.5 and 1.1; workgroups 1.8, 0.6, 3.3 and 0.27 (1.6 ps and
+    // 1.3 ns where the box is not staged).  Lanes take 0.21 ps a pixel, but never less than 13 us and 43 ns a
+    // pixel, one lane's walk.  Box 1764, us of the three wave layouts: 300 points 8.5, 5.7, 4.4; 6020 15.2, 14.4,
+    // 20.9; 15050 29.6, 30.0, 45.1.  38400 points, lanes and waves: box 234 23, 32; 1279 73, 56; 27836 935, 670.
+    // 1e6 points: box 1279 347, 1248; 27836 4258, 17079.
+    const double box = bx * by, np = (double)pts, inf = HUGE_VAL;
+    const double side = std::max(bx, by);
+    const double t1 = side <= kLcAxis ? std::hypot(3.2e3 + 2.9 * box, np * (0.62 + 0.58e-3 * box)) : inf;
+    const double t4 = side <= kLcAxis ? std::hypot(3.5e3 + 1.1 * box, np * (0.75 + 0.63e-3 * box)) : inf;
+    const bool wide = side > kLcAxis * kLcWaves;
+    const double tg = std::hypot(3.3e3 + (wide ? 1.3 : 0.27) * box, np * (1.8 + (wide ? 1.6e-3 : 0.6e-3) * box));
     const double t_lane = std::max(np * (0.02 + 0.21e-3 * box), 13e3 + 43.0 * box);
-    const bool lanes = a.path == 1 || (a.path == 0 && t_lane < t_wave);
+    const bool lanes = a.path == 1 || (a.path == 0 && t_lane < std::min(tg, std::min(t1, t4)));
     if (lanes) {
         const int64_t blocks = (pts + 255) / 256;
         if (blocks > 0x7fffffff) return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_light_curve_lanes, dim3((unsigned)blocks), dim3(256), 0, s, a);
     } else {
+        // (the grid limit holds for one wave per point, whichever layout is taken)
         const int64_t blocks = (pts + kLcWaves - 1) / kLcWaves;
         if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_light_curve, dim3((unsigned)blocks), dim3(64 * kLcWaves), 0, s, a);
+        const dim3 blk(64 * kLcWaves);
+        if (tg < t1 && tg < t4 && pts <= 0x7fffffff)
+            hipLaunchKernelGGL((k_light_curve<kLcWaves, kLcAhead>), dim3((unsigned)pts), blk, 0, s, a);
+        else if (t4 < t1) hipLaunchKernelGGL((k_light_curve<1, kLcAhead>), dim3((unsigned)blocks), blk, 0, s, a);
+        else hipLaunchKernelGGL((k_light_curve<1, 1>), dim3((unsigned)blocks), blk, 0, s, a);
     }
     return hipGetLastError();
 }
