@@ -694,7 +694,7 @@ struct ZoomLayout {
     int64_t P = 2;                            // cells per parent side between levels
     int64_t lcw1[rs::kZoomLevels] = {}, lcw2[rs::kZoomLevels] = {}, lnx[rs::kZoomLevels] = {}, lny[rs::kZoomLevels] = {};
     size_t list_off[rs::kZoomLevels] = {};
-    size_t part_off = 0, total = 0;
+    size_t start_off = 0, cells_off = 0, part_off = 0, total = 0;
 };
 
 int zoom_layout(const rs_job *job, const rs_zoom *z, const Tune &t, ZoomLayout &L)
@@ -741,6 +741,10 @@ int zoom_layout(const rs_job *job, const rs_zoom *z, const Tune &t, ZoomLayout &
         L.list_off[l] = off;
         off += align256((size_t)(L.lnx[l] * L.lny[l]) * sizeof(uint32_t));
     }
+    L.start_off = off;
+    off += align256((size_t)(L.ncy + 1) * sizeof(uint64_t));
+    L.cells_off = off;
+    off += align256((size_t)L.ncy * sizeof(uint32_t));
     L.part_off = off;
     off += (size_t)partial_words(job) * sizeof(uint32_t);
     L.total = off + 256;
@@ -1038,15 +1042,17 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     // [3] rays per lane block, [4 + l] kept cells of the coarser level l < levels - 1, [8] work counter of
     // the shoot, [kZoomQueue + l] of level l
     static_assert(rs::kZoomLevels <= 5, "the statistics block holds four coarser levels");
-    hipError_t e = rs::launch_fill_u32(stats, rs::kZoomQueue + rs::kZoomLevels, 0u, s);
-    if (e == hipSuccess) e = rs::launch_fill_u32(stats + 1, 1, (uint32_t)L.cells, s);
-    if (e == hipSuccess) e = rs::launch_fill_u32(stats + 2, 1, (uint32_t)L.S, s);
-    if (e == hipSuccess) e = rs::launch_fill_u32(stats + 3, 1, (uint32_t)(t.K1 * t.K2), s);
-    if (e != hipSuccess) return dev_fail(e, "zoom statistics reset");
     const rs_raygrid &g = job->grid;
-    if (g.win_n[0] == 0 || g.win_n[1] == 0) return RS_OK;
-
+    const bool empty = g.win_n[0] == 0 || g.win_n[1] == 0;
     uint32_t *part = reinterpret_cast<uint32_t *>(base + L.part_off);
+    // (the list's and the partial maps' parts of the workspace are whole 16-byte words)
+    rs::ZoomInit zi{stats, (uint32_t)L.cells, (uint32_t)L.S, (uint32_t)(t.K1 * t.K2),
+                    reinterpret_cast<uint4 *>(base + L.list_off[L.levels - 1]), reinterpret_cast<uint4 *>(part),
+                    empty || t.K1 != 1 ? 0 : (L.cells + 3) / 4, empty ? 0 : partial_words(job) / 4};
+    hipError_t e = rs::launch_zoom_init(zi, s);
+    if (e != hipSuccess) return dev_fail(e, "zoom reset");
+    if (empty) return RS_OK;
+
     const int64_t pstride = partial_stride(job);
     const int64_t bins = (int64_t)job->map.n[0] * job->map.n[1];
     rs::DirectArgs a = make_args(job, t, part, pstride, opts);
@@ -1093,6 +1099,7 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     z.time = a.time;
     z.list = z.lists[L.levels - 1];
     z.stats = stats;
+    z.flags = t.K1 == 1;
 
     rs::CellBlocks cb{};
     cb.list = z.list;
@@ -1103,13 +1110,16 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     cb.ncx = L.ncx;
     cb.sx = L.sx;
     cb.S = L.S;
+    cb.ncy = L.ncy;
+    cb.groups = L.S / L.sx;
+    cb.cells = reinterpret_cast<uint32_t *>(base + L.cells_off);
+    cb.start = reinterpret_cast<uint64_t *>(base + L.start_off);
     const int64_t max_groups = (L.cells * L.S + rs::kThreads - 1) / rs::kThreads;
 
-    e = rs::launch_zero(part, partial_words(job), s);
-    if (e != hipSuccess) return dev_fail(e, "zero partial maps");
     e = rs::launch_zoom_mark(z, s);
+    if (e == hipSuccess && z.flags) e = rs::launch_zoom_rows(cb, z.list, s);
     if (e != hipSuccess) return dev_fail(e, "zoom culling launch");
-    if (t.K1 == 1) e = rs::launch_split_cells(a, t.run(), t.LT, cb, L.cells * L.S, s);
+    if (t.K1 == 1) e = rs::launch_split_cells(a, t.run(), t.LT, cb, s);
     else e = rs::launch_direct_cells(a, t.K1, t.K2, t.run(), t.LT, cb, max_groups, s);
     if (e != hipSuccess) return dev_fail(e, "zoom direct-sum launch");
     e = rs::launch_reduce(part, bins, pstride, job->counts, reinterpret_cast<unsigned long long *>(job->n_lost), s);

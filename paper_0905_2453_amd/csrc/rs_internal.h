@@ -186,21 +186,41 @@ struct ZoomArgs {
     const float2 *vel;                  // lens velocities or null
     double time;
     uint32_t *lists[kZoomLevels];       // kept cells of each level; the last is `list`
-    uint32_t *list;                     // kept cell indices (finest level)
+    uint32_t *list;                     // kept cell indices (finest level); with `flags` a flag per cell
+    int32_t flags;
     uint32_t *stats;                    // [0] cells kept (list length), [4 + l] kept at level l < levels - 1,
                                         // [kZoomQueue + l] work counter of level l
 };
 
+// What a zoom's first launch sets: the statistics block (zeros but for [1..3]), 16-byte words of flags and of
+// partial maps to clear.
+struct ZoomInit {
+    uint32_t *stats, cells, blocks, rays;
+    uint4 *flags, *part;
+    int64_t n_flags, n_part;
+};
+hipError_t launch_zoom_init(const ZoomInit &z, hipStream_t s);
 hipError_t launch_zoom_mark(const ZoomArgs &z, hipStream_t s);
 hipError_t launch_advance(const float4 *in, const float2 *vel, int64_t n, double time, float4 *out, hipStream_t s);
-// Lane blocks (K1 columns x K2 rows) of the culling cells in list[0 .. *count).
+// Columns that a group of four ray rows of a row of cells counts at least when its blocks are cut into items.
+constexpr int kMinColumns = 32;
+
+// Lane blocks (K1 columns x K2 rows) of the kept culling cells: list[0 .. *count).
 struct CellBlocks {
     const uint32_t *list;
     const uint32_t *count;
     uint32_t *queue;        // work counter of the split kernel, zeroed before each launch
     int64_t c1, c2, ncx;    // culling cell size (window columns, rows) and cells per row
     int64_t sx, S;          // lane blocks per cell row, lane blocks per cell
+    // The split kernel's form: list holds each row of cells at my ncx, the row's cells[my] kept columns of
+    // cells in order; start[my] items (64 lane blocks each) come before those of row my, start[ncy] in all.
+    int64_t ncy, groups;    // rows of cells, groups of four ray rows of a cell
+    uint32_t *cells;
+    uint64_t *start;
 };
+
+// Turn the flags of a zoom's cells into the split kernel's form of CellBlocks.
+hipError_t launch_zoom_rows(const CellBlocks &cb, uint32_t *list, hipStream_t s);
 
 // Persistent direct sum over the lane blocks of the listed cells.
 hipError_t launch_direct_cells(const DirectArgs &a, int K1, int K2, int T, int LT, const CellBlocks &cb,
@@ -234,7 +254,7 @@ hipError_t launch_direct(const DirectArgs &a, int K1, int K2, int T, int LT, int
 // One-column blocks, lenses split over a workgroup's waves: a window, the lane blocks of a cell list, a batch
 // (WV waves a workgroup, split_batched_waves of the batch's blocks and largest lens count).
 hipError_t launch_split(const DirectArgs &a, int T, int LT, hipStream_t s);
-hipError_t launch_split_cells(const DirectArgs &a, int T, int LT, const CellBlocks &cb, int64_t blocks, hipStream_t s);
+hipError_t launch_split_cells(const DirectArgs &a, int T, int LT, const CellBlocks &cb, hipStream_t s);
 int split_batched_waves(uint64_t blocks, int64_t most_lenses);
 hipError_t launch_split_batched(const BatchArgs &b, int T, int LT, int WV, int grid, hipStream_t s);
 int split_batched_occupancy(int T, int LT, int WV);

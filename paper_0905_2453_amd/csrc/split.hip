@@ -5,7 +5,7 @@
 // over the lenses as partial sums over subsets); section 3.2 eq. 6.
 //
 // Work decomposition.  The WV waves of a workgroup share 64 blocks of four rays: lane l holds column
-// c0 + l, rows r0 .. r0 + 3 (or its own block out of a list of culling cells).  Wave w sums the groups of
+// c0 + l, rows r0 .. r0 + 3 (or its own block of the kept culling cells).  Wave w sums the groups of
 // T kQuadRuns lenses w, w + WV, w + 2 WV, ... of the field; every group is summed operation by operation as
 // k_direct sums it, and the waves' FP64 sums meet in LDS in wave order.  FP64 addition of the groups'
 // float32 sums is exact while they stay within 2^29 of each other (24-bit numbers in a 53-bit sum), so
@@ -18,21 +18,31 @@ namespace rs {
 
 namespace {
 
-// Where the four rays of a lane lie: on rows that all lanes share, on rows of the lane's own, or each at
-// a random point of its cell.
-enum RayMode { kSharedRows = 0, kOwnRows = 1, kJitter = 2 };
+// Where the four rays of a lane lie: on rows that all lanes share, on one of up to kRowGroups consecutive
+// groups of four rows, or each at a random point of its cell.
+enum RayMode { kSharedRows = 0, kGroupRows = 1, kJitter = 2 };
+constexpr int kRowGroups = 3;
+static_assert((kMinColumns - 1 + 63) / kMinColumns + 1 <= kRowGroups, "64 blocks in a row meet kRowGroups groups");
+
+// kGroupRows: window row of the first group, groups of the workgroup's blocks, the lane's one.
+struct RowGroups {
+    uint32_t first;
+    int n, mine;
+};
 
 // B lenses are staged by a wave at a time (private to it: the lens loop has no barrier).
-template <int B, int WV>
+template <int B, int WV, int G = 1>
 struct SplitSmem {
+    static constexpr int kGroups = G;
     union {
         struct {
-            float4 dy[WV][B];    // kSharedRows: x2 - x2_i of the four rows; else the lens record
-            float2 xm[WV][B];    // kSharedRows: x1_i and the mass
+            float4 dy[WV][B * G];   // kJitter: the lens record; else x2 - x2_i of the four rows, of each row group
+            float2 xm[WV][B];       // x1_i and the mass
         } st;
         double2 sum[WV][4][64];  // the waves' sums, after the lens loop
         uint32_t win[kMaxWindow * kMaxWindow];
     };
+    float4 rows[G];   // kGroupRows: x2 of the groups' rows
     uint32_t bad[64];
     int cand[2][8];
     uint32_t lost;
@@ -48,15 +58,15 @@ __device__ __forceinline__ void wave_fence()
 
 // One float32 run of T staged lenses for the lane's four rays: the arithmetic of shoot_rays with four
 // rows per reciprocal.
-template <int T, RayMode MODE, int B, int WV>
-__device__ __forceinline__ void quad_run(const SplitSmem<B, WV> &sm, int wave, int at, const float *x1, const float *x2,
-                                         float *s1, float *s2)
+template <int T, RayMode MODE, int B, int WV, int G>
+__device__ __forceinline__ void quad_run(const SplitSmem<B, WV, G> &sm, int wave, int at, int mine, const float *x1,
+                                         const float *x2, float *s1, float *s2)
 {
 #pragma unroll
     for (int j = 0; j < T; ++j) {
         float dx[4], dx2[4], dy[4], q[4], m;
-        const float4 l = sm.st.dy[wave][at + j];
-        if constexpr (MODE == kSharedRows) {
+        const float4 l = sm.st.dy[wave][(at + j) * G + mine];
+        if constexpr (MODE != kJitter) {
             const float2 xm = sm.st.xm[wave][at + j];
             m = xm.y;
             dx[0] = x1[0] - xm.x;
@@ -69,7 +79,7 @@ __device__ __forceinline__ void quad_run(const SplitSmem<B, WV> &sm, int wave, i
 #pragma unroll
             for (int e = 0; e < 4; ++e) dy[e] = x2[e] - l.y;
 #pragma unroll
-            for (int e = 0; e < (MODE == kJitter ? 4 : 1); ++e) dx[e] = x1[e] - l.x;
+            for (int e = 0; e < 4; ++e) dx[e] = x1[e] - l.x;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -99,10 +109,14 @@ __device__ __forceinline__ void quad_run(const SplitSmem<B, WV> &sm, int wave, i
 // ds_read_b128: 24 FP32 instructions and a reciprocal per lens and four rays, where every lane subtracting
 // them itself takes 28.  1e5 lenses, 4096^2 rays: 192.4 ms (8.72e12 interactions/s), k_direct 206.3 ms on the
 // same box; 512^2 rays, which fill a quarter of the chip's wave slots as blocks of 1024: 3.5 ms, k_direct 8.0.
-template <int T, int B, int WV, RayMode MODE, bool DUMP>
+//
+// kGroupRows differs in that the lens's differences are staged for each of the workgroup's row groups, and
+// a lane reads its own's (adjacent 16-byte words: no bank conflict).
+template <int T, int B, int WV, RayMode MODE, bool DUMP, int G>
 __device__ __forceinline__ void shoot_split(const DirectArgs &a, uint32_t c0, uint32_t r0, int64_t cmax, int64_t rmin,
-                                            int64_t rmax, uint32_t group, SplitSmem<B, WV> &sm)
+                                            int64_t rmax, uint32_t group, SplitSmem<B, WV, G> &sm, RowGroups rg = {})
 {
+    static_assert(MODE == kGroupRows || G == 1, "row groups");
     constexpr int GS = T * kQuadRuns, NG = B / GS, PL = B / 64, NX = MODE == kJitter ? 4 : 1;
     static_assert(B % GS == 0 && B % 64 == 0 && (GS & (GS - 1)) == 0 && WV >= 4, "staging shape");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -114,6 +128,12 @@ __device__ __forceinline__ void shoot_split(const DirectArgs &a, uint32_t c0, ui
         if (e < NX) x1[e] = ray_coord(a.glo1, a.gt1, g1, MODE == kJitter ? jitter_u(a.jkey1, r) : 0.5) * kLoopScale;
         x2[e] = ray_coord(a.glo2, a.gt2, g2, MODE == kJitter ? jitter_u(a.jkey2, r) : 0.5) * kLoopScale;
         if (MODE == kSharedRows) x2[e] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x2[e])));
+    }
+    if (MODE == kGroupRows) {
+        if (tid < 4 * rg.n)
+            reinterpret_cast<float *>(sm.rows)[tid] =
+                ray_coord(a.glo2, a.gt2, a.wlo2 + rg.first + tid, 0.5) * kLoopScale;
+        __syncthreads();
     }
 
     // the wave's k-th group is group k WV + wave of the field; staged lens `at` belongs to its group
@@ -144,6 +164,12 @@ __device__ __forceinline__ void shoot_split(const DirectArgs &a, uint32_t c0, ui
             if constexpr (MODE == kSharedRows) {
                 sm.st.dy[wave][p * 64 + lane] = make_float4(x2[0] - l.y, x2[1] - l.y, x2[2] - l.y, x2[3] - l.y);
                 sm.st.xm[wave][p * 64 + lane] = make_float2(l.x, l.z);
+            } else if constexpr (MODE == kGroupRows) {
+                for (int g = 0; g < rg.n; ++g) {
+                    const float4 r = sm.rows[g];
+                    sm.st.dy[wave][(p * 64 + lane) * G + g] = make_float4(r.x - l.y, r.y - l.y, r.z - l.y, r.w - l.y);
+                }
+                sm.st.xm[wave][p * 64 + lane] = make_float2(l.x, l.z);
             } else {
                 sm.st.dy[wave][p * 64 + lane] = l;
             }
@@ -158,7 +184,7 @@ __device__ __forceinline__ void shoot_split(const DirectArgs &a, uint32_t c0, ui
 #pragma unroll
                 for (int h = 0; h < kQuadRuns; ++h) {
                     float s1[4], s2[4];
-                    quad_run<T, MODE>(sm, wave, k * GS + h * T, x1, x2, s1, s2);
+                    quad_run<T, MODE>(sm, wave, k * GS + h * T, rg.mine, x1, x2, s1, s2);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         m1[e] = h == 0 ? s1[e] : m1[e] + s1[e];
@@ -172,7 +198,7 @@ __device__ __forceinline__ void shoot_split(const DirectArgs &a, uint32_t c0, ui
                 const int runs = (int)((left + T - 1) / T);
                 for (int h = 0; h < runs; ++h) {
                     float s1[4], s2[4];
-                    quad_run<T, MODE>(sm, wave, k * GS + h * T, x1, x2, s1, s2);
+                    quad_run<T, MODE>(sm, wave, k * GS + h * T, rg.mine, x1, x2, s1, s2);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         m1[e] += s1[e];
@@ -209,9 +235,9 @@ __device__ __forceinline__ void shoot_split(const DirectArgs &a, uint32_t c0, ui
         if (!__builtin_isfinite(B1 + B2)) sm.bad[lane] = 1u;
     }
     const int64_t row = (int64_t)r0 + (owner ? wave : 0);
-    const int64_t g1 = a.wlo1 + c0, g2 = a.wlo2 + row, rg = g2 * a.gn1 + g1;
-    const float X1 = ray_coord(a.glo1, a.gt1, g1, MODE == kJitter ? jitter_u(a.jkey1, rg) : 0.5) * kLoopScale;
-    const float X2 = ray_coord(a.glo2, a.gt2, g2, MODE == kJitter ? jitter_u(a.jkey2, rg) : 0.5) * kLoopScale;
+    const int64_t g1 = a.wlo1 + c0, g2 = a.wlo2 + row, id = g2 * a.gn1 + g1;
+    const float X1 = ray_coord(a.glo1, a.gt1, g1, MODE == kJitter ? jitter_u(a.jkey1, id) : 0.5) * kLoopScale;
+    const float X2 = ray_coord(a.glo2, a.gt2, g2, MODE == kJitter ? jitter_u(a.jkey2, id) : 0.5) * kLoopScale;
     __syncthreads();
     if (owner && sm.bad[lane]) {
         // see shoot_rays: a block with a non-finite sum is redone with one reciprocal per ray, in the same
@@ -310,33 +336,48 @@ __global__ void __launch_bounds__(64 * WV, kSimdWaves<WV>) k_split(const DirectA
     split_tile<T, B, WV, DUMP, JIT>(a, blockIdx.x, blockIdx.x, sm);
 }
 
-// Persistent form over the lane blocks of a list of culling cells; see k_direct_cells for how block j of
-// cell list[i] is cut.  Workgroups take 64 blocks at a time from the counter cb.queue until none are left.
+// Persistent form over the blocks of the kept culling cells.  The blocks of a row of cells are counted through
+// group of four ray rows by group, the columns of the row's kept cells in order, so that 64 of them lie on at most
+// kRowGroups groups and share the rows' differences as k_split's do (groups of fewer than kMinColumns columns are
+// padded).  Workgroups take 64 blocks at a time from the counter cb.queue until none are left.  89 170 kept cells
+// of 3 x 24 rays, 1e5 lenses: 76.2 ms, each lane subtracting rows of its own 80.0.
 template <int T, int B, int WV, bool JIT>
 __global__ void __launch_bounds__(64 * WV, kSimdWaves<WV>) k_split_cells(const DirectArgs a, const CellBlocks cb)
 {
-    __shared__ SplitSmem<B, WV> sm;
+    __shared__ SplitSmem<B, WV, JIT ? 1 : kRowGroups> sm;
     __shared__ uint32_t s_item;
-    const uint64_t n = (uint64_t)(*cb.count) * (uint64_t)cb.S;
+    const int lane = threadIdx.x & 63;
+    const uint64_t n = cb.start[cb.ncy];
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(cb.queue, 1u);
         __syncthreads();
-        const uint32_t item = s_item;
-        const uint64_t q = (uint64_t)item * 64 + (threadIdx.x & 63);
-        if ((uint64_t)item * 64 >= n) break;
-        int64_t c0 = 0, r0 = 0, cmax = 0, rmin = 0, rmax = 0;
-        if (q < n) {
-            const uint64_t i = q / (uint64_t)cb.S;
-            const int64_t j = (int64_t)(q - i * (uint64_t)cb.S);
-            const int64_t cell = cb.list[i];
-            const int64_t mx = cell % cb.ncx, my = cell / cb.ncx;
-            c0 = mx * cb.c1 + j % cb.sx;
-            rmin = my * cb.c2 + a.rskip;
-            r0 = (rmin & ~int64_t(3)) + (j / cb.sx) * 4;
-            cmax = min((mx + 1) * cb.c1, a.wn1);
-            rmax = min((my + 1) * cb.c2 + a.rskip, a.wn2);
+        const uint32_t item = __builtin_amdgcn_readfirstlane(s_item);
+        if (item >= n) break;
+        // the row of cells with start[my] <= item < start[my + 1], a 64th of the rows left at a time
+        int64_t my = 0;
+        for (int64_t left = cb.ncy; left > 1;) {
+            const int64_t step = (left + 63) / 64, at = lane * step;
+            const int k = __popcll(__ballot(at < left && cb.start[my + (at < left ? at : 0)] <= item)) - 1;
+            my += k * step;
+            left = min(step, left - k * step);
         }
-        shoot_split<T, B, WV, JIT ? kJitter : kOwnRows, false>(a, (uint32_t)c0, (uint32_t)r0, cmax, rmin, rmax, item, sm);
+        const uint32_t cols = cb.cells[my] * (uint32_t)cb.c1, padded = max(cols, (uint32_t)kMinColumns);
+        const uint64_t j0 = (item - cb.start[my]) * 64;
+        const uint32_t g0 = (uint32_t)(j0 / padded), rest = (uint32_t)(j0 - (uint64_t)g0 * padded);
+        const uint32_t g = g0 + (rest + lane) / padded, col = (rest + lane) % padded;
+        const uint32_t groups = (uint32_t)cb.groups, last = min(g0 + (rest + 63) / padded, groups - 1);
+        const int64_t rmin = my * cb.c2 + a.rskip, base = rmin & ~int64_t(3);
+        int64_t c0 = 0, cmax = 0;
+        if (g < groups && col < cols) {
+            const uint32_t k = col / (uint32_t)cb.c1;
+            const int64_t mx = cb.list[my * cb.ncx + k];
+            c0 = mx * cb.c1 + (col - k * (uint32_t)cb.c1);
+            cmax = min((mx + 1) * cb.c1, a.wn1);
+        }
+        const RowGroups rg{(uint32_t)(base + 4 * (int64_t)g0), (int)(last - g0) + 1, JIT ? 0 : (int)(min(g, last) - g0)};
+        shoot_split<T, B, WV, JIT ? kJitter : kGroupRows, false>(a, (uint32_t)c0, (uint32_t)(base + 4 * (int64_t)min(g, last)),
+                                                                 cmax, rmin, min((my + 1) * cb.c2 + a.rskip, a.wn2), item,
+                                                                 sm, rg);
         __syncthreads();
     }
 }
@@ -387,7 +428,7 @@ hipError_t launch(const DirectArgs &a, hipStream_t s)
 }
 
 template <int T, int B, int WV>
-hipError_t launch_cells(const DirectArgs &a, const CellBlocks &cb, int64_t max_groups, hipStream_t s)
+hipError_t launch_cells(const DirectArgs &a, const CellBlocks &cb, hipStream_t s)
 {
     int occ = 0, dev = 0, cus = 0;
     const hipError_t e = a.jitter
@@ -397,7 +438,11 @@ hipError_t launch_cells(const DirectArgs &a, const CellBlocks &cb, int64_t max_g
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 256;
-    const dim3 g((unsigned)std::min<int64_t>((int64_t)std::max(1, occ) * std::max(1, cus), max_groups)), blk(64 * WV);
+    // 64 blocks at a time of every row of cells, were all of them kept
+    const int64_t cols = std::max<int64_t>(cb.ncx * cb.c1, kMinColumns);
+    const int64_t fit = (int64_t)std::max(1, occ) * std::max(1, cus);
+    const int64_t most = cb.ncy * ((cb.groups * cols + 63) / 64);
+    const dim3 g((unsigned)std::min(fit, most)), blk(64 * WV);
     if (a.jitter) hipLaunchKernelGGL((k_split_cells<T, B, WV, true>), g, blk, 0, s, a, cb);
     else hipLaunchKernelGGL((k_split_cells<T, B, WV, false>), g, blk, 0, s, a, cb);
     return hipGetLastError();
@@ -446,12 +491,11 @@ hipError_t launch_split(const DirectArgs &a, int T, int LT, hipStream_t s)
     RS_SPLIT_SWITCH(T, LT, wv, launch, a, s);
 }
 
-hipError_t launch_split_cells(const DirectArgs &a, int T, int LT, const CellBlocks &cb, int64_t blocks, hipStream_t s)
+hipError_t launch_split_cells(const DirectArgs &a, int T, int LT, const CellBlocks &cb, hipStream_t s)
 {
-    const int64_t groups = (blocks + 63) / 64;
-    if (groups <= 0) return hipSuccess;
+    if (cb.ncx <= 0 || cb.ncy <= 0) return hipSuccess;
     const int wv = a.n_lens >= 2048 ? 8 : 4;
-    RS_SPLIT_SWITCH(T, LT, wv, launch_cells, a, cb, groups, s);
+    RS_SPLIT_SWITCH(T, LT, wv, launch_cells, a, cb, s);
 }
 
 // Four waves a workgroup: eight leave more waves without lenses in a batch's small fields (64 maps of 128^2 to 512^2

@@ -77,6 +77,7 @@ __device__ __forceinline__ void zoom_run(const float4 *L, float cf1, float cf2, 
 //   level 0: every cell of the coarsest level;
 //   level l > 0: the cells inside the cells kept at level l - 1: item t takes child t % P^2 of
 //                kept cell lists[l - 1][t / P^2].
+// With z.flags the last level sets a flag per kept cell instead (k_zoom_rows lists them by row).
 // A child's rectangle lies inside its parent's, so a cell whose image can meet the map is kept
 // at every level above it.
 //
@@ -243,14 +244,101 @@ __global__ void __launch_bounds__(64 * kZoomWaves, 4) k_zoom_mark(const ZoomArgs
             if (!keep)
                 keep = (y1 + E1 >= z.zlo1) && (y1 - E1 <= z.zhi1) && (y2 + E2 >= z.zlo2) && (y2 - E2 <= z.zhi2);
             if (keep && active && part == 0) {
-                uint32_t *cnt = level == z.levels - 1 ? &z.stats[0] : &z.stats[4 + level];
-                z.lists[level][atomicAdd(cnt, 1u)] = (uint32_t)idx;
+                if (level == z.levels - 1 && z.flags) {
+                    atomicAdd(&z.stats[0], 1u);
+                    z.list[idx] = 1u;
+                } else {
+                    uint32_t *cnt = level == z.levels - 1 ? &z.stats[0] : &z.stats[4 + level];
+                    z.lists[level][atomicAdd(cnt, 1u)] = (uint32_t)idx;
+                }
             }
         }
     }
 }
 
+// Everything a zoom clears or sets before its kernels, in one launch: the statistics, the cells' flags, the partial maps.
+__global__ void __launch_bounds__(256) k_zoom_init(const ZoomInit z)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x, first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (first < kZoomQueue + kZoomLevels)
+        z.stats[first] = first == 1 ? z.cells : first == 2 ? z.blocks : first == 3 ? z.rays : 0u;
+    for (int64_t i = first; i < z.n_flags; i += stride) z.flags[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int64_t i = first; i < z.n_part; i += stride) z.part[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// A row of cells per workgroup at a time: its kept cells' columns, in order, to the front of the row's part of the
+// list (in place: a place is written after the flags up to it are read), and the items they make (CellBlocks).
+__global__ void __launch_bounds__(1024) k_zoom_rows(const CellBlocks cb, uint32_t *list)
+{
+    __shared__ uint32_t s_wave[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int64_t my = blockIdx.x; my < cb.ncy; my += gridDim.x) {
+        uint32_t *row = list + my * cb.ncx;
+        uint32_t kept = 0;
+        for (int64_t i0 = 0; i0 < cb.ncx; i0 += 1024) {
+            const bool k = i0 + tid < cb.ncx && row[i0 + tid] != 0u;
+            const unsigned long long b = __ballot(k);
+            if (lane == 0) s_wave[wave] = (uint32_t)__popcll(b);
+            __syncthreads();
+            uint32_t before = kept;
+            for (int w = 0; w < 16; ++w) {
+                if (w == wave) before = kept;
+                kept += s_wave[w];
+            }
+            if (k) row[before + __popcll(b & ((1ull << lane) - 1))] = (uint32_t)(i0 + tid);
+            __syncthreads();
+        }
+        if (tid == 0) {
+            cb.cells[my] = kept;
+            const uint64_t cols = kept ? max((uint64_t)kept * (uint64_t)cb.c1, (uint64_t)kMinColumns) : 0;
+            cb.start[my] = (cols * (uint64_t)cb.groups + 63) / 64;
+        }
+    }
+}
+
+// Exclusive scan of start[0 .. ncy) in place, the sum to start[ncy], with one workgroup.
+__global__ void __launch_bounds__(1024) k_zoom_row_scan(const CellBlocks cb)
+{
+    __shared__ uint64_t part[1024];
+    const int tid = threadIdx.x;
+    const int64_t per = (cb.ncy + 1023) / 1024, b = min(cb.ncy, tid * per), e = min(cb.ncy, b + per);
+    uint64_t s = 0;
+    for (int64_t i = b; i < e; ++i) s += cb.start[i];
+    part[tid] = s;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+        const uint64_t v = tid >= off ? part[tid - off] : 0;
+        __syncthreads();
+        part[tid] += v;
+        __syncthreads();
+    }
+    uint64_t run = part[tid] - s;
+    for (int64_t i = b; i < e; ++i) {
+        const uint64_t v = cb.start[i];
+        cb.start[i] = run;
+        run += v;
+    }
+    if (tid == 1023) cb.start[cb.ncy] = part[1023];
+}
+
 }  // namespace
+
+hipError_t launch_zoom_init(const ZoomInit &z, hipStream_t s)
+{
+    const int64_t blocks = std::min<int64_t>(8192, std::max<int64_t>(1, (std::max(z.n_flags, z.n_part) + 255) / 256));
+    hipLaunchKernelGGL(k_zoom_init, dim3((unsigned)blocks), dim3(256), 0, s, z);
+    return hipGetLastError();
+}
+
+hipError_t launch_zoom_rows(const CellBlocks &cb, uint32_t *list, hipStream_t s)
+{
+    if (cb.ncx <= 0 || cb.ncy <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_zoom_rows, dim3((unsigned)std::min<int64_t>(cb.ncy, 4096)), dim3(1024), 0, s, cb, list);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_zoom_row_scan, dim3(1), dim3(1024), 0, s, cb);
+    return hipGetLastError();
+}
 
 hipError_t launch_zoom_mark(const ZoomArgs &z, hipStream_t s)
 {
