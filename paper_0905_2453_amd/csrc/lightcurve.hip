@@ -194,10 +194,11 @@ __device__ __forceinline__ uint4 load4(const uint32_t *p)
 // The pixels of a row inside the support are one run of columns: |c - y| grows with the distance of the column,
 // rounded or not.  Its ends are estimated with a square root and settled by the plain definition's own FP64
 // inclusion test, so the included set is that of testing every pixel; the pixels between them take no test (14
-// FP64 instructions a pixel of the box before, 6 a pixel inside and about 30 a row now), and their counts come four
-// to a load.  Row sums take the row's Gaussian factor once.
-// Bound: FP64 issue and the L1 lines that the lanes of a load touch.  1e6 points, 1024^2 map, 21 x 21-pixel box: 258 us
-// (testing every pixel of the box 449); error against 80-bit sums 2.6e-16 (7.9e-16) rms.
+// FP64 instructions a pixel of the box before, 6 a pixel inside and about 45 a row now), and their counts come four
+// to a load.  Row sums take the row's Gaussian factor once.  The settling loops end at their first test as a rule: four
+// tests unrolled were half of a row's instructions (266 us).
+// Bound: FP64 issue and the L1 lines that the lanes of a load touch.  1e6 points, 1024^2 map, 21 x 21-pixel box: 192 us
+// (testing every pixel of the box 480); error against 80-bit sums 2.6e-16 (7.9e-16) rms.
 __global__ void __launch_bounds__(256) k_light_curve_lanes(const LightArgs a)
 {
     const int64_t gp = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -231,9 +232,11 @@ __global__ void __launch_bounds__(256) k_light_curve_lanes(const LightArgs a)
         double gy = rec ? exp(-dy0 * dy0 * h) : 1.0;
         double ry = rec ? exp(-(2.0 * dy0 * w2 + w2 * w2) * h) : 1.0;
         const double ky = rec ? exp(-2.0 * w2 * w2 * h) : 1.0;
-        // the source's place in columns, and what rounding may move a column's place by (in columns)
+        // the source's place in columns, and what rounding may move a column's place or the end of a run by (in
+        // columns; a rounding of R^2 moves the end by up to 3e-8 R)
         const double mid = (ys1 - a.lo[0]) * a.inv_w[0] - 0.5;
-        const double slack = 1e-3 + 0x1p-46 * (fabs(a.lo[0]) + (double)a.n[0] * w1 + fabs(ys1)) * a.inv_w[0];
+        const double slack =
+            1e-3 + (1e-7 * rs + 0x1p-46 * (fabs(a.lo[0]) + (double)a.n[0] * w1 + fabs(ys1))) * a.inv_w[0];
         for (int p2 = p2lo; p2 <= p2hi; ++p2) {
             const double dy = (a.lo[1] + ((double)p2 + 0.5) * w2) - ys2;
             const double dy2 = dy * dy;
@@ -244,15 +247,34 @@ __global__ void __launch_bounds__(256) k_light_curve_lanes(const LightArgs a)
             };
             if (dy2 <= rs2) {
                 // estimated ends, widened by more than the estimate's error, then moved in to where the test
-                // holds; first ends past last when no pixel of the row is inside
+                // holds (mostly at once, so the loops are not unrolled); first ends past last when no pixel of the
+                // row is inside
                 const double half = __builtin_amdgcn_sqrt(rs2 - dy2) * a.inv_w[0];
                 const double reach = half + (half * 1e-6 + slack);
-                int first = (int)fmin(fmax(floor(mid - reach), (double)p1lo), (double)p1hi);
-                int last = (int)fmin(fmax(ceil(mid + reach), (double)p1lo), (double)p1hi);
+                int first = (int)fmin(fmax(ceil(mid - reach), (double)p1lo), (double)p1hi);
+                int last = (int)fmin(fmax(floor(mid + reach), (double)p1lo), (double)p1hi);
+#pragma clang loop unroll(disable) vectorize(disable)
                 while (first <= last && !inside(first)) ++first;
+#pragma clang loop unroll(disable) vectorize(disable)
                 while (last > first && !inside(last)) --last;
                 const uint32_t *row = a.counts + (int64_t)k * a.frame_stride + (int64_t)p2 * a.n[0];
                 double sn = 0.0, sw = 0.0;
+                // the run's counts in order, four to a load; the last one to three come with the four that end the run
+                // (four requested ahead, too: 100 VGPRs instead of 78, and slower, 208 us against 192)
+                auto walk = [&](auto add4, auto add) __attribute__((always_inline)) {
+                    int p1 = first;
+                    if (p1 + 3 <= last) {
+                        const uint4 tail = load4(row + last - 3);
+                        for (; p1 + 3 <= last; p1 += 4) add4(load4(row + p1));
+                        const int rest = last - p1 + 1;
+                        if (rest > 2) add(tail.y);
+                        if (rest > 1) add(tail.z);
+                        if (rest > 0) add(tail.w);
+                    } else {
+#pragma clang loop unroll(disable) vectorize(disable)
+                        for (; p1 <= last; ++p1) add(row[p1]);
+                    }
+                };
                 if (rec) {
                     double gx = gx0, rx = rx0;
                     for (int p1 = p1lo; p1 < first; ++p1) {
@@ -265,15 +287,12 @@ __global__ void __launch_bounds__(256) k_light_curve_lanes(const LightArgs a)
                         gx *= rx;
                         rx *= kx;
                     };
-                    int p1 = first;
-                    for (; p1 + 3 <= last; p1 += 4) {
-                        const uint4 n = load4(row + p1);
+                    walk([&](const uint4 &n) {
                         add(n.x);
                         add(n.y);
                         add(n.z);
                         add(n.w);
-                    }
-                    for (; p1 <= last; ++p1) add(row[p1]);
+                    }, add);
                     num = fma(gy, sn, num);
                     den = fma(gy, sw, den);
                 } else if (gauss) {
@@ -284,12 +303,8 @@ __global__ void __launch_bounds__(256) k_light_curve_lanes(const LightArgs a)
                         den += wgt;
                     }
                 } else {
-                    int p1 = first;
-                    for (; p1 + 3 <= last; p1 += 4) {
-                        const uint4 n = load4(row + p1);
-                        sn += ((double)n.x + (double)n.y) + ((double)n.z + (double)n.w);
-                    }
-                    for (; p1 <= last; ++p1) sn += (double)row[p1];
+                    walk([&](const uint4 &n) { sn += ((double)n.x + (double)n.y) + ((double)n.z + (double)n.w); },
+                         [&](uint32_t n) { sn += (double)n; });
                     num += sn;
                     den += (double)(last - first + 1);
                 }
@@ -316,19 +331,19 @@ hipError_t launch_light_curve(const LightArgs &a, hipStream_t s)
     const double by = std::min(std::ceil(2.0 * a.support * a.inv_w[1]) + 2.0, (double)a.n[1]);
     // Which layout is faster, from what each measured over 50 to 1e6 points and boxes of 15 to 6e4 pixels: the
     // time of one point on an idle GPU and the time that a point of very many adds, combined as a root of
-    // squares.  Waves take 0.62 ns a point and 0.58 ps a pixel of its box, but 3.2 us and 2.9 ns a pixel one by
-    // one; with pixels requested ahead 0.75, 0.63, 3.5 and 1.1; workgroups 1.8, 0.6, 3.3 and 0.27 (1.6 ps and
-    // 1.3 ns where the box is not staged).  Lanes take 0.21 ps a pixel, but never less than 13 us and 43 ns a
+    // squares.  Waves take 0.75 ns a point and 0.58 ps a pixel of its box, but 3.2 us and 2.9 ns a pixel one by
+    // one; with pixels requested ahead 0.85, 0.63, 3.5 and 1.1; workgroups 1.9, 0.6, 3.3 and 0.27 (1.6 ps and
+    // 1.3 ns where the box is not staged).  Lanes take 0.2 ps a pixel, but never less than 7.5 us and 39 ns a
     // pixel, one lane's walk.  Box 1764, us of the three wave layouts: 300 points 8.5, 5.7, 4.4; 6020 15.2, 14.4,
-    // 20.9; 15050 29.6, 30.0, 45.1.  38400 points, lanes and waves: box 234 23, 32; 1279 73, 56; 27836 935, 670.
-    // 1e6 points: box 1279 347, 1248; 27836 4258, 17079.
+    // 20.9; 15050 29.6, 30.0, 45.1.  38400 points, lanes and waves: box 234 15, 32; 1279 52, 56; 27836 866, 668.
+    // 1e6 points: box 1279 238, 1250; 27836 4340, 17100.
     const double box = bx * by, np = (double)pts, inf = HUGE_VAL;
     const double side = std::max(bx, by);
-    const double t1 = side <= kLcAxis ? std::hypot(3.2e3 + 2.9 * box, np * (0.62 + 0.58e-3 * box)) : inf;
-    const double t4 = side <= kLcAxis ? std::hypot(3.5e3 + 1.1 * box, np * (0.75 + 0.63e-3 * box)) : inf;
+    const double t1 = side <= kLcAxis ? std::hypot(3.2e3 + 2.9 * box, np * (0.75 + 0.58e-3 * box)) : inf;
+    const double t4 = side <= kLcAxis ? std::hypot(3.5e3 + 1.1 * box, np * (0.85 + 0.63e-3 * box)) : inf;
     const bool wide = side > kLcAxis * kLcWaves;
-    const double tg = std::hypot(3.3e3 + (wide ? 1.3 : 0.27) * box, np * (1.8 + (wide ? 1.6e-3 : 0.6e-3) * box));
-    const double t_lane = std::max(np * (0.02 + 0.21e-3 * box), 13e3 + 43.0 * box);
+    const double tg = std::hypot(3.3e3 + (wide ? 1.3 : 0.27) * box, np * (1.9 + (wide ? 1.6e-3 : 0.6e-3) * box));
+    const double t_lane = std::max(np * (0.04 + 0.2e-3 * box), 7.5e3 + 39.0 * box);
     const bool lanes = a.path == 1 || (a.path == 0 && t_lane < std::min(tg, std::min(t1, t4)));
     if (lanes) {
         const int64_t blocks = (pts + 255) / 256;
