@@ -24,7 +24,7 @@ namespace rs {
 namespace {
 
 constexpr int kZoomRun = 16;     // float32 run length before the FP64 combine
-constexpr int kZoomWaves = 16;   // waves of a workgroup, each with every kZoomWaves-th chunk of 64 lenses
+constexpr int kZoomWaves = 8;    // waves of a workgroup, each with every kZoomWaves-th chunk of 64 lenses
 constexpr int kZoomSums = 8;
 
 __device__ __forceinline__ float4 zoom_pad_lens()
@@ -82,16 +82,19 @@ __device__ __forceinline__ void zoom_run(const float4 *L, float cf1, float cf2, 
 // at every level above it.
 //
 // Persistent: a workgroup takes 64 / ks cells at a time from the level's counter.  Its waves split the lenses
-// (wave w sums the chunks of 64 lenses w, w + 16, ..., staged privately), and ks (1, 2 or 4) consecutive
+// (wave w sums the chunks of 64 lenses w, w + 8, ..., staged privately), and ks (1, 2 or 4) consecutive
 // lanes share a cell, each summing every ks-th run of the chunks; the partial sums meet in a fixed butterfly
 // and then in LDS in wave order.  A level has few cells (15 000 to 140 000 on the benchmark's zoom), so a lane
 // that sums a cell alone, or a sixteenth of it, leaves most wave slots empty (1.8 waves per SIMD on average).  The
 // Taylor terms are summed without a look at the distance and redone for the rare run that holds a near lens.
-// The five levels of that zoom (1e5 lenses): 16.1 ms, 31.0 before both changes.
+// The five levels of that zoom (1e5 lenses): 16.1 ms, 31.0 before both changes.  Lanes that share a cell read
+// different runs at once: with a place skipped after each run these lie on different banks, and with eight waves two
+// workgroups fit a compute unit, one's merge under the other's sums: 14.3 ms (runs on the same banks 16.1, the skip
+// alone 15.1; 30 000 lenses: 2.45, 2.17, both 2.02).
 __global__ void __launch_bounds__(64 * kZoomWaves, 4) k_zoom_mark(const ZoomArgs z, int level, int ks)
 {
     __shared__ union {
-        float4 lens[kZoomWaves][64];
+        float4 lens[kZoomWaves][64 + 64 / kZoomRun];   // a place is skipped after each run
         double sum[kZoomWaves][kZoomSums][64];
     } sm;
     __shared__ uint32_t s_inside[64];
@@ -154,11 +157,11 @@ __global__ void __launch_bounds__(64 * kZoomWaves, 4) k_zoom_mark(const ZoomArgs
         float4 nxt = zoom_pad_lens();
         if (wave < n_chunks) nxt = fetch(wave);
         for (int64_t c = wave; c < n_chunks; c += kZoomWaves) {
-            sm.lens[wave][lane] = nxt;
+            sm.lens[wave][lane + lane / kZoomRun] = nxt;
             zoom_wave_fence();
             if (c + kZoomWaves < n_chunks) nxt = fetch(c + kZoomWaves);
             for (int r = part * kZoomRun; r < 64; r += ks * kZoomRun) {
-                const float4 *L = &sm.lens[wave][r];
+                const float4 *L = &sm.lens[wave][r + r / kZoomRun];
                 float s1, s2, sd, so, sc, sp, sq, rmin;
                 zoom_run<false>(L, cf1, cf2, near2, s1, s2, sd, so, sc, sp, sq, rmin);
                 // (keeps the Taylor sums in the loop above: moved behind the branch, their terms would all
