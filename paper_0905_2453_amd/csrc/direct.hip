@@ -441,7 +441,8 @@ template <int K1, int K2, int T, int LT, bool DUMP, bool JIT>
 __global__ void __launch_bounds__(kThreads) k_direct(const DirectArgs a)
 {
     __shared__ TileSmem<LT> sm;
-    shoot_tile<K1, K2, T, LT, DUMP, JIT>(a, blockIdx.x, blockIdx.x, sm);
+    const uint32_t tile = (uint32_t)group_number();
+    shoot_tile<K1, K2, T, LT, DUMP, JIT>(a, tile, tile, sm);
 }
 
 // Persistent direct sum over the lane blocks of a list of culling cells (the cells a zoom
@@ -562,7 +563,7 @@ __global__ void __launch_bounds__(256) k_reduce(const uint32_t *partial, int64_t
 template <int K1, int K2, int T, int LT>
 hipError_t launch_kt(const DirectArgs &a, int64_t n_tiles, hipStream_t s)
 {
-    const dim3 g((unsigned)n_tiles), blk(kThreads);
+    const dim3 g = group_dim3(n_tiles, kThreads), blk(kThreads);
     if (a.jitter) {
         if (a.ray_y) hipLaunchKernelGGL((k_direct<K1, K2, T, LT, true, true>), g, blk, 0, s, a);
         else hipLaunchKernelGGL((k_direct<K1, K2, T, LT, false, true>), g, blk, 0, s, a);

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch_grid.h"
 #include "rs.h"
 
 namespace rs {
@@ -19,6 +20,14 @@ constexpr int kLostStride = 16;
 constexpr int64_t kLostWords = 2 * kLostSlots * kLostStride;           // 8 KiB after the partial maps
 constexpr int kNoAllocBins = 1 << 20;   // largest map rs_shoot_noalloc takes (1024 x 1024 bins)
 constexpr int64_t kNoAllocWords = (int64_t)kPartials * kNoAllocBins + kLostWords;   // its fixed scratch
+
+inline dim3 group_dim3(int64_t n, int threads)
+{
+    const GroupGrid g = group_grid(n, threads);
+    return dim3(g.x, g.y);
+}
+// Number of the workgroup in a group_grid launch.
+__device__ __forceinline__ int64_t group_number() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 
 // Everything one direct-sum launch needs, already reduced to FP64 constants on the host.
 struct DirectArgs {

@@ -333,7 +333,8 @@ template <int T, int B, int WV, bool DUMP, bool JIT>
 __global__ void __launch_bounds__(64 * WV, kSimdWaves<WV>) k_split(const DirectArgs a)
 {
     __shared__ SplitSmem<B, WV> sm;
-    split_tile<T, B, WV, DUMP, JIT>(a, blockIdx.x, blockIdx.x, sm);
+    const uint32_t tile = (uint32_t)group_number();
+    split_tile<T, B, WV, DUMP, JIT>(a, tile, tile, sm);
 }
 
 // Persistent form over the blocks of the kept culling cells.  The blocks of a row of cells are counted through
@@ -416,7 +417,7 @@ __global__ void __launch_bounds__(64 * WV, kSimdWaves<WV>) k_split_batched(const
 template <int T, int B, int WV>
 hipError_t launch(const DirectArgs &a, hipStream_t s)
 {
-    const dim3 g(a.n_blocks), blk(64 * WV);
+    const dim3 g = group_dim3(a.n_blocks, 64 * WV), blk(64 * WV);
     if (a.jitter) {
         if (a.ray_y) hipLaunchKernelGGL((k_split<T, B, WV, true, true>), g, blk, 0, s, a);
         else hipLaunchKernelGGL((k_split<T, B, WV, false, true>), g, blk, 0, s, a);
