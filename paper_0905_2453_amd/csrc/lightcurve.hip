@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(64 * kLcWaves) k_light_curve(const LightArgs a
     __shared__ double2 s_row[kPoints][kLcAxis * SPLIT];   // (d2^2, g(d2)) per box row
     __shared__ double s_sum[kLcWaves][2];
     const int lane = threadIdx.x % kLanes, wv = threadIdx.x / kLanes;
-    const int64_t gp = (int64_t)blockIdx.x * kPoints + wv;
+    const int64_t gp = group_number() * kPoints + wv;
     const bool active = gp < (int64_t)a.n_tracks * a.n_points;
     int64_t tr = 0;
     int k = 0;
@@ -201,7 +201,7 @@ __device__ __forceinline__ uint4 load4(const uint32_t *p)
 // (testing every pixel of the box 480); error against 80-bit sums 2.6e-16 (7.9e-16) rms.
 __global__ void __launch_bounds__(256) k_light_curve_lanes(const LightArgs a)
 {
-    const int64_t gp = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t gp = group_number() * 256 + threadIdx.x;
     if (gp >= (int64_t)a.n_tracks * a.n_points) return;
     const int64_t tr = gp / a.n_points;
     const int k = (int)(gp - tr * a.n_points);
@@ -348,16 +348,16 @@ hipError_t launch_light_curve(const LightArgs &a, hipStream_t s)
     if (lanes) {
         const int64_t blocks = (pts + 255) / 256;
         if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_light_curve_lanes, dim3((unsigned)blocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_light_curve_lanes, group_dim3(blocks, 256), dim3(256), 0, s, a);
     } else {
-        // (the grid limit holds for one wave per point, whichever layout is taken)
         const int64_t blocks = (pts + kLcWaves - 1) / kLcWaves;
         if (blocks > 0x7fffffff) return hipErrorInvalidValue;
         const dim3 blk(64 * kLcWaves);
-        if (tg < t1 && tg < t4 && pts <= 0x7fffffff)
-            hipLaunchKernelGGL((k_light_curve<kLcWaves, kLcAhead>), dim3((unsigned)pts), blk, 0, s, a);
-        else if (t4 < t1) hipLaunchKernelGGL((k_light_curve<1, kLcAhead>), dim3((unsigned)blocks), blk, 0, s, a);
-        else hipLaunchKernelGGL((k_light_curve<1, 1>), dim3((unsigned)blocks), blk, 0, s, a);
+        const dim3 g = group_dim3(blocks, 64 * kLcWaves);
+        if (tg < t1 && tg < t4)
+            hipLaunchKernelGGL((k_light_curve<kLcWaves, kLcAhead>), group_dim3(pts, 64 * kLcWaves), blk, 0, s, a);
+        else if (t4 < t1) hipLaunchKernelGGL((k_light_curve<1, kLcAhead>), g, blk, 0, s, a);
+        else hipLaunchKernelGGL((k_light_curve<1, 1>), g, blk, 0, s, a);
     }
     return hipGetLastError();
 }
