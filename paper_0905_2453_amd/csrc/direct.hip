@@ -684,7 +684,7 @@ hipError_t launch_direct(const DirectArgs &a, int K1, int K2, int T, int LT, int
     return hipErrorInvalidValue;
 }
 
-// several-column blocks (the one-column ones are in split.hip)
+// several-column blocks (one-column ones: split.hip, and k_batched<1, 4> for a batch's jobs of few lenses)
 #define RS_BLOCK_SWITCH(FN, ...)                                              \
     if (K1 == 2 && K2 == 2) return FN<2, 2>(__VA_ARGS__);                     \
     if (K1 == 2 && K2 == 4) return FN<2, 4>(__VA_ARGS__);                     \
@@ -694,6 +694,7 @@ hipError_t launch_direct(const DirectArgs &a, int K1, int K2, int T, int LT, int
 
 hipError_t launch_batched(const BatchArgs &b, int K1, int K2, int T, int LT, int grid, hipStream_t s)
 {
+    if (K1 == 1 && K2 == 4) return launch_b<1, 4>(b, T, LT, grid, s);
     RS_BLOCK_SWITCH(launch_b, b, T, LT, grid, s)
     return hipErrorInvalidValue;
 }
@@ -708,6 +709,7 @@ hipError_t launch_direct_cells(const DirectArgs &a, int K1, int K2, int T, int L
 
 int batched_occupancy(int K1, int K2, int T, int LT)
 {
+    if (K1 == 1 && K2 == 4) return occ_b<1, 4>(T, LT);
     RS_BLOCK_SWITCH(occ_b, T, LT)
     return 0;
 }

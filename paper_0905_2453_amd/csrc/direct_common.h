@@ -16,8 +16,10 @@ __device__ __forceinline__ float ray_coord(double lo, double t, int64_t i, doubl
     return (float)w;
 }
 
+// (The launch's constants `a` below are DirectArgs in any address space.)
 // Half-open source pixel of y; returns p2 * n1 + p1, or -1 when the ray is lost.
-__device__ __forceinline__ int pixel_of(double y1, double y2, const DirectArgs &a, int &p1, int &p2)
+template <class Args>
+__device__ __forceinline__ int pixel_of(double y1, double y2, const Args &a, int &p1, int &p2)
 {
     double f1 = floor((y1 - a.mlo1) * a.ms1);
     double f2 = floor((y2 - a.mlo2) * a.ms2);
@@ -44,7 +46,8 @@ constexpr double kLoopBack = kRcpBiasComp * 0.0625;
 constexpr int kQuadRuns = 4;
 
 // Lens i as the loop reads it: moved to the launch's time, coordinates scaled.
-__device__ __forceinline__ float4 loop_lens(const DirectArgs &a, int64_t i)
+template <class Args>
+__device__ __forceinline__ float4 loop_lens(const Args &a, int64_t i)
 {
     float4 l = moved_lens(a.lenses[i], a.vel, i, a.time);
     l.x *= kLoopScale;
@@ -55,7 +58,8 @@ __device__ __forceinline__ float4 loop_lens(const DirectArgs &a, int64_t i)
 // Zero-mass padding of the last lens tile: at lens 0's position, so that its squared distances are
 // ordinary numbers (products stay finite and its terms are exactly zero); a ray exactly there takes
 // the per-ray recomputation below, as a ray on lens 0 does anyway.
-__device__ __forceinline__ float4 pad_lens(const DirectArgs &a)
+template <class Args>
+__device__ __forceinline__ float4 pad_lens(const Args &a)
 {
     float4 l = loop_lens(a, 0);
     l.z = 0.0f;
@@ -86,7 +90,8 @@ __device__ __forceinline__ void window_origin(const int *c1, const int *c2, int 
 
 // Counter of lost rays for the i-th workgroup: one of lost_mask + 1, a cache line apart (additions to one
 // address complete one after the other, about 12 ns each).
-__device__ __forceinline__ unsigned long long *lost_slot(const DirectArgs &a, uint32_t i)
+template <class Args>
+__device__ __forceinline__ unsigned long long *lost_slot(const Args &a, uint32_t i)
 {
     return a.lost + (size_t)(i & a.lost_mask) * kLostStride;
 }

@@ -138,6 +138,12 @@ void use_partials(rs::DirectArgs &a, uint32_t *part)
     a.lost_mask = rs::kLostSlots - 1;
 }
 
+// 64-column x 4-row blocks of the window.
+int64_t block_count(const rs_job *job)
+{
+    return ((job->grid.win_n[0] + 63) / 64) * ((kernel_rows(job->grid) + 3) / 4);
+}
+
 // Device-side description of one job for a K1 x K2 ray block; counts go to `partial`.
 rs::DirectArgs make_args(const rs_job *job, const Tune &t, uint32_t *partial, int64_t pstride,
                          const rs_opts *opts)
@@ -177,7 +183,7 @@ rs::DirectArgs make_args(const rs_job *job, const Tune &t, uint32_t *partial, in
     a.jkey2 = rs::jitter_key(g.jitter_seed, 1);
     a.vel = reinterpret_cast<const float2 *>(job->velocities);
     a.time = job->time;
-    a.n_blocks = (uint32_t)(((g.win_n[0] + 63) / 64) * ((a.wn2 + 3) / 4));
+    a.n_blocks = (uint32_t)block_count(job);
     a.per_item = 1;
     return a;
 }
@@ -226,23 +232,39 @@ struct GraphKey {
     void *ws;
     int device, K1, K2, T, LT, W, grid, n_jobs;
     uint32_t n_items;
-    int waves;
+    int waves, split_grid, split_jobs;
+    uint32_t split_items;
     bool operator<(const GraphKey &o) const
     {
-        return std::tie(ws, device, K1, K2, T, LT, W, grid, n_jobs, n_items, waves) <
-               std::tie(o.ws, o.device, o.K1, o.K2, o.T, o.LT, o.W, o.grid, o.n_jobs, o.n_items, o.waves);
+        return std::tie(ws, device, K1, K2, T, LT, W, grid, n_jobs, n_items, waves, split_grid, split_jobs, split_items) <
+               std::tie(o.ws, o.device, o.K1, o.K2, o.T, o.LT, o.W, o.grid, o.n_jobs, o.n_items, o.waves, o.split_grid,
+                        o.split_jobs, o.split_items);
     }
 };
 std::map<GraphKey, hipGraphExec_t> g_graphs;
 constexpr size_t kMaxGraphs = 32;
 
 struct PreparedBatch {
-    rs::BatchArgs args{};
+    rs::BatchArgs args{};       // the jobs of k_batched ...
+    rs::BatchArgs split{};      // ... and those before them in the table, of k_split_batched
+    uint32_t first = 0;         // item at which the former begin
     uint64_t interactions = 0;  // ray-lens interactions of the items taken
-    int grid = 0;
+    int grid = 0, split_grid = 0;
     int device = 0;
-    int waves = 0;              // waves of a workgroup that split the lenses (one-column blocks)
+    int waves = 0;              // waves of a workgroup of k_split_batched
 };
+
+// Whether a job of a batch of `blocks` one-column blocks takes k_split_batched.  Its workgroup takes a quarter of the
+// rays of k_batched's, which fills the GPU where the latter's tiles are few, but does its fixed part and takes its item
+// (12 ns) four times as often, and adds its counts four times as often to the job's one map, without an LDS window: few
+// lenses on a map of a few pixels are bound by additions to one cache line.  us of k_split_batched and k_batched:
+// 8 x 2048^2 rays, 64 lenses 535, 429; 100 647, 657; 500 2118, 2228; 2000 7839, 8410; all on one pixel, 4 x 2048^2 rays,
+// 100 lenses 1650, 358; 500 2673, 1131; 3000 5894, 6285; one map of 1000^2 rays: 100 lenses 74, 52; 300 77, 82; of
+// 512^2: 100 lenses 35, 34; 300 36, 50; of 256^2: 64 lenses 18, 27.
+bool split_job(const rs_job &j, uint64_t blocks)
+{
+    return j.n_lens >= 512 || (j.n_lens >= 256 && blocks < 4096) || blocks < 512;
+}
 
 // Validate, order by decreasing work per tile, upload the job table into the workspace and fill
 // the kernel arguments.  With `scratch`, every job's counts and lost counter are redirected to a
@@ -276,15 +298,20 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     std::vector<uint8_t> host(table_bytes + start_bytes);
     auto *args = reinterpret_cast<rs::DirectArgs *>(host.data());
     auto *start = reinterpret_cast<uint32_t *>(host.data() + table_bytes);
-    // Work items: a tile of rays, or of one-column blocks as many as make up about 2048 lenses' work (an item
-    // taken from the counter costs about 12 ns), and at least so many that their number stays below that of
-    // the tiles where it could pass 2^31.
+    // Work items: a tile of rays, or (k_split_batched) of one-column blocks as many as make up about 2048 lenses' work
+    // (an item taken from the counter costs about 12 ns) but no more than leaves 6144 items, four to a workgroup that
+    // the GPU holds (16 blocks of 300 lenses, six an item 49 us, one 17), and so many that the items stay fewer
+    // than the tiles where they could pass 2^31.
     uint64_t items = 0, taken = 0, inter = 0, tiles = 0, blocks = 0;
-    for (int32_t k = 0; k < n_jobs; ++k) tiles += (uint64_t)tile_count(&jobs[k], t);
+    for (int32_t k = 0; k < n_jobs; ++k) {
+        tiles += (uint64_t)tile_count(&jobs[k], t);
+        blocks += (uint64_t)block_count(&jobs[k]);
+    }
     if (tiles >= (uint64_t(1) << 31)) return fail(RS_ERANGE, "more than 2^31 ray tiles in one batch");
     const int64_t least = tiles >= (uint64_t(1) << 29) ? rs::kWaves : 1;
     const uint64_t rays_per_tile = 64ull * (uint64_t)t.K1 * (uint64_t)rs::kWaves * (uint64_t)t.K2;
     start[0] = 0;
+    int32_t n_split = 0;
     for (int32_t k = 0; k < n_jobs; ++k) {
         const rs_job *job = &jobs[order[k]];
         uint32_t *counts = job->counts;
@@ -298,12 +325,15 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
         }
         int64_t nt = tile_count(job, t);
         uint64_t rays_per_item = rays_per_tile;
-        if (t.K1 == 1) {
-            const int64_t q = std::max(least, std::min<int64_t>(16, 2048 / std::max<int64_t>(job->n_lens, 1)));
+        if (t.K1 == 1 && split_job(*job, blocks)) {
+            const int64_t q = std::max<int64_t>(least, std::min<int64_t>({16, 2048 / std::max<int64_t>(job->n_lens, 1),
+                                                                          (int64_t)(blocks / 6144)}));
             args[k].per_item = (uint32_t)q;
-            blocks += args[k].n_blocks;
+            n_split = k + 1;   // (the jobs are in order of their lenses)
             nt = ((int64_t)args[k].n_blocks + q - 1) / q;
             rays_per_item = 256ull * (uint64_t)q;
+        } else if (t.K1 == 1) {
+            args[k].window = t.W >= 0 ? t.W : 64;
         }
         items += (uint64_t)nt;
         start[k + 1] = (uint32_t)items;
@@ -318,10 +348,11 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return dev_fail(e, "device query");
-    if (t.K1 == 1) pb.waves = rs::split_batched_waves(blocks, n_jobs > 0 ? jobs[order[0]].n_lens : 0);
-    const int occ = t.K1 == 1 ? rs::split_batched_occupancy(t.run(), t.LT, pb.waves)
-                              : rs::batched_occupancy(t.K1, t.K2, t.run(), t.LT);
-    if (occ <= 0) return fail(RS_EINTERNAL, "no occupancy for the batched kernel");
+    pb.first = std::min<uint32_t>(start[n_split], (uint32_t)taken);
+    if (n_split > 0) pb.waves = rs::split_batched_waves(blocks, jobs[order[0]].n_lens);
+    const int split_occ = n_split > 0 ? rs::split_batched_occupancy(t.run(), t.LT, pb.waves) : 1;
+    const int occ = n_split < n_jobs ? rs::batched_occupancy(t.K1, t.K2, t.run(), t.LT) : 1;
+    if (occ <= 0 || split_occ <= 0) return fail(RS_EINTERNAL, "no occupancy for the batched kernel");
 
     {
         std::lock_guard<std::mutex> lk(g_mu);
@@ -334,28 +365,35 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
         e = hipMemcpyAsync(base + L.start_off, keep.data() + table_bytes, start_bytes, hipMemcpyHostToDevice, s);
         if (e != hipSuccess) return dev_fail(e, "job table upload");
     }
-    pb.args.jobs = reinterpret_cast<const rs::DirectArgs *>(base + L.table_off);
-    pb.args.item_start = reinterpret_cast<const uint32_t *>(base + L.start_off);
-    pb.args.n_jobs = n_jobs;
-    pb.args.n_items = (uint32_t)taken;
-    pb.args.queue = reinterpret_cast<uint32_t *>(base + L.queue_off);
+    auto *table = reinterpret_cast<const rs::DirectArgs *>(base + L.table_off);
+    auto *item_start = reinterpret_cast<const uint32_t *>(base + L.start_off);
+    auto *queue = reinterpret_cast<uint32_t *>(base + L.queue_off);
+    pb.split = {table, item_start, n_split, pb.first, queue};
+    pb.args = {table + n_split, item_start + n_split, n_jobs - n_split, (uint32_t)taken, queue + 1};
     pb.interactions = item_budget ? inter : 0;
-    pb.grid = (int)std::min<uint64_t>(std::max<uint64_t>(taken, 1), (uint64_t)cus * (uint64_t)occ);
+    auto groups = [&](uint64_t n, int o) { return (int)std::min<uint64_t>(n, (uint64_t)cus * (uint64_t)o); };
+    pb.split_grid = groups(pb.first, split_occ);
+    pb.grid = groups(taken - pb.first, occ);
     pb.device = dev;
     return RS_OK;
 }
 
-// Reset the work counter and run the persistent kernel, captured once into a graph per
-// (workspace, shape, grid, batch size) and replayed afterwards; the legacy default stream cannot
-// be captured, so there the two kernels are launched directly.
+// Reset the work counters and run the persistent kernels, captured once into a graph per
+// (workspace, shape, grids, batch size) and replayed afterwards; the legacy default stream cannot
+// be captured, so there the kernels are launched directly.
 int run_batch(const PreparedBatch &pb, const Tune &t, void *workspace, hipStream_t s, bool use_graph)
 {
     if (pb.args.n_items == 0) return RS_OK;
     auto enqueue = [&]() -> hipError_t {
-        hipError_t e = rs::launch_fill_u32(pb.args.queue, 1, 0u, s);
-        if (e == hipSuccess)
-            e = t.K1 == 1 ? rs::launch_split_batched(pb.args, t.run(), t.LT, pb.waves, pb.grid, s)
-                          : rs::launch_batched(pb.args, t.K1, t.K2, t.run(), t.LT, pb.grid, s);
+        hipError_t e = hipSuccess;
+        if (pb.split_grid > 0) {
+            e = rs::launch_fill_u32(pb.split.queue, 1, 0u, s);
+            if (e == hipSuccess) e = rs::launch_split_batched(pb.split, t.run(), t.LT, pb.waves, pb.split_grid, s);
+        }
+        if (pb.grid > 0) {
+            if (e == hipSuccess) e = rs::launch_fill_u32(pb.args.queue, 1, pb.first, s);
+            if (e == hipSuccess) e = rs::launch_batched(pb.args, t.K1, t.K2, t.run(), t.LT, pb.grid, s);
+        }
         return e;
     };
     if (!use_graph || s == nullptr) {
@@ -363,7 +401,7 @@ int run_batch(const PreparedBatch &pb, const Tune &t, void *workspace, hipStream
         return e == hipSuccess ? RS_OK : dev_fail(e, "batched launch");
     }
     const GraphKey key{workspace, pb.device, t.K1, t.K2, t.run(), t.LT, t.W, pb.grid, pb.args.n_jobs, pb.args.n_items,
-                       pb.waves};
+                       pb.waves, pb.split_grid, pb.split.n_jobs, pb.split.n_items};
     hipGraphExec_t exec = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_mu);

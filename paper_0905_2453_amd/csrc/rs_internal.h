@@ -97,8 +97,8 @@ struct BatchArgs {
     const DirectArgs *jobs;     // n_jobs descriptors
     const uint32_t *item_start; // n_jobs + 1 prefix sums of ray tiles per job
     int32_t n_jobs;
-    uint32_t n_items;           // work items to take this launch (<= item_start[n_jobs])
-    uint32_t *queue;            // work-item counter, zeroed before each launch
+    uint32_t n_items;           // work items end here (<= item_start[n_jobs])
+    uint32_t *queue;            // work-item counter, set to item_start[0] before each launch
 };
 
 // ---------------------------------------------------------------- learned far field

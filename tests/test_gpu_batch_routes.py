@@ -1,0 +1,65 @@
+"""GPU checks of a batch's choice of kernel per job: lens counts and numbers of blocks on both sides of each limit,
+batches that hold jobs of both kernels, random ray positions, moving lenses, empty windows, explicit map windows.
+Every job's counts and lost rays must be those of its own rs_shoot call, on the first pass and on replays.
+"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# (lenses, columns, rows, jitter seed, moving) of each job; float32 run, staged tile, map window
+BATCHES = [
+    ([(255, 640, 1000, None, False), (256, 1000, 40, 3, False)], 0, 0, 0),           # under 4096 blocks, both kernels
+    ([(256, 700, 1600, None, True), (300, 64, 100, None, False)], 0, 0, 0),          # 4425: the second kernel alone
+    ([(511, 900, 1200, None, False), (512, 300, 333, 5, True), (0, 70, 50, None, False)], 0, 0, 0),   # both
+    ([(3, 130, 679, None, False), (0, 64, 4, None, False), (64, 5, 400, 7, False)], 0, 0, 0),         # 511 blocks
+    ([(3, 130, 679, None, False), (0, 64, 4, None, False), (64, 5, 404, 7, False)], 0, 0, 0),         # 512
+    ([(40, 1024, 1024, None, False)] * 3 + [(2000, 200, 200, None, False)], 0, 0, -1),
+    ([(40, 1024, 1024, None, False), (700, 512, 512, None, False)], 32, 512, 32),
+    ([(100, 0, 10, None, False), (100, 200, 100, None, False), (1000, 10, 0, None, False)], 16, 0, 64),
+]
+
+
+@pytest.mark.parametrize("case", range(len(BATCHES)))
+def test_batch_equals_single_maps(case):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_0905_2453_amd as P
+    P.lib()
+    specs, run, tile, window = BATCHES[case]
+    print(f"batch {case}: {specs}", flush=True)
+    o = P.Opts()
+    o.block_cols, o.block_rows, o.fp32_run, o.lens_tile, o.map_window = 1, 4, run, tile, window
+    g = torch.Generator(device="cuda").manual_seed(case)
+    args, single = [], []
+    for n, w1, w2, jitter, moving in specs:
+        lenses = torch.rand((n, 4), device="cuda", generator=g)
+        lenses[:, :2] = 30.0 * lenses[:, :2] - 15.0
+        vel = 0.2 * torch.randn((n, 2), device="cuda", generator=g) if moving else None
+        args.append((lenses, 0.1, 0.2, (-12.0, -11.0), (12.0, 13.0), (w1 + 9, w2 + 5), (-7.0, -6.0), (6.0, 7.0), (50, 41),
+                     ((3, 2), (w1, w2)), jitter, vel, 0.7))
+
+    def job(a):
+        counts = torch.zeros((41, 50), dtype=torch.int32, device="cuda")
+        lost = torch.zeros(1, dtype=torch.int64, device="cuda")
+        return P.make_job(*a[:9], counts, lost, *a[9:]), counts, lost
+
+    for a in args:
+        j, counts, lost = job(a)
+        P.shoot_job(j, torch.empty(P.workspace_bytes(j, o), dtype=torch.uint8, device="cuda"), o)
+        single.append((counts.cpu(), int(lost.item())))
+        assert int(counts.sum()) + single[-1][1] == a[9][1][0] * a[9][1][1]
+    jobs = [job(a) for a in args]
+    ws = torch.empty(P.batched_workspace_bytes([j[0] for j in jobs]), dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    for rep in range(3):
+        with torch.cuda.stream(stream):
+            for _, counts, lost in jobs:
+                counts.zero_()
+                lost.zero_()
+            P.shoot_batched([j[0] for j in jobs], ws, o, stream=stream)
+        stream.synchronize()
+        for k, ((_, counts, lost), (want, want_lost)) in enumerate(zip(jobs, single)):
+            assert torch.equal(counts.cpu(), want) and int(lost.item()) == want_lost, (rep, k)
+    P.release_graphs()
