@@ -150,7 +150,8 @@ typedef struct {
                                 16 with several); one-column blocks add four runs in float32
                                 before each FP64 addition, several-column blocks add each run  */
     int32_t map_window;      /* side of the LDS-privatised map window: 16, 32 or 64; -1 = off   */
-                             /* (default: off with one-column blocks, 64 with several columns)  */
+                             /* (default: off with one-column blocks outside batches, else 64; */
+                             /* kernels that split a field's lenses over waves have none)       */
     double *ray_y;           /* optional device output, 2 doubles per ray of the window        */
     int32_t *ray_pix;        /* optional device output, pixel p2*n1+p1 per ray, -1 = lost      */
     uint32_t flags;          /* RS_FLAG_*                                                      */

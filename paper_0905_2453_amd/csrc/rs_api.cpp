@@ -256,17 +256,18 @@ struct PreparedBatch {
 
 // Whether a job of a batch of `blocks` one-column blocks takes k_split_batched.  Its workgroup takes a quarter of the
 // rays of k_batched's, which fills the GPU where the latter's tiles are few, but does its fixed part and takes its item
-// (12 ns) four times as often, and adds its counts four times as often to the job's one map, without an LDS window: few
-// lenses on a map of a few pixels are bound by additions to one cache line.  us of k_split_batched and k_batched:
-// 8 x 2048^2 rays, 64 lenses 535, 429; 100 647, 657; 500 2118, 2228; 2000 7839, 8410; all on one pixel, 4 x 2048^2 rays,
-// 100 lenses 1650, 358; 500 2673, 1131; 3000 5894, 6285; one map of 1000^2 rays: 100 lenses 74, 52; 300 77, 82; of
-// 512^2: 100 lenses 35, 34; 300 36, 50; of 256^2: 64 lenses 18, 27.
+// (12 ns) four times as often, and adds its counts to the job's one map without an LDS window: fewer lenses on a map
+// of few pixels are bound by additions to a cache line.  us of k_split_batched and k_batched: 8 x 2048^2 rays, 64
+// lenses 535, 429; 100 647, 657; 500 2118, 2228; 2000 7839, 8410; on 4 x 4 pixels, 4 x 2048^2 rays, 512 lenses 1348,
+// 1140, 1000 lenses 2190, 2196; one map of 1000^2 rays: 100 lenses 74, 52; 256 71, 66; 511 96, 112; of 512^2: 100
+// lenses 35, 34; 300 36, 50; of 256^2: 64 lenses 18, 27.
 bool split_job(const rs_job &j, uint64_t blocks)
 {
-    return j.n_lens >= 512 || (j.n_lens >= 256 && blocks < 4096) || blocks < 512;
+    const bool few_pixels = (int64_t)j.map.n[0] * j.map.n[1] <= 1024;
+    return j.n_lens >= (few_pixels ? 1024 : 512) || blocks < 8 * (uint64_t)std::max<int64_t>(64, j.n_lens);
 }
 
-// Validate, order by decreasing work per tile, upload the job table into the workspace and fill
+// Validate, order by kernel and decreasing work per tile, upload the job table into the workspace and fill
 // the kernel arguments.  With `scratch`, every job's counts and lost counter are redirected to a
 // scratch map inside the workspace (used by the autotuner).  At most `item_budget` ray-lens
 // interactions worth of items are taken (0 = all).
@@ -288,10 +289,20 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     if (ws_bytes < L.total) return fail(RS_ESMALLBUF, "workspace %zu bytes < %zu needed", ws_bytes, L.total);
     uint8_t *base = reinterpret_cast<uint8_t *>(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
 
+    uint64_t tiles = 0, blocks = 0;
+    for (int32_t k = 0; k < n_jobs; ++k) {
+        tiles += (uint64_t)tile_count(&jobs[k], t);
+        blocks += (uint64_t)block_count(&jobs[k]);
+    }
+    if (tiles >= (uint64_t(1) << 31)) return fail(RS_ERANGE, "more than 2^31 ray tiles in one batch");
     std::vector<int32_t> order(n_jobs);
     std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return jobs[a].n_lens > jobs[b].n_lens; });
+    auto split = [&](int32_t k) { return t.K1 == 1 && split_job(jobs[k], blocks); };
+    const auto whole = std::stable_partition(order.begin(), order.end(), split);
+    auto costlier = [&](int32_t a, int32_t b) { return jobs[a].n_lens > jobs[b].n_lens; };
+    std::stable_sort(order.begin(), whole, costlier);
+    std::stable_sort(whole, order.end(), costlier);
+    const int32_t n_split = (int32_t)(whole - order.begin());
 
     const size_t table_bytes = (size_t)n_jobs * sizeof(rs::DirectArgs);
     const size_t start_bytes = ((size_t)n_jobs + 1) * sizeof(uint32_t);
@@ -302,16 +313,10 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     // (an item taken from the counter costs about 12 ns) but no more than leaves 6144 items, four to a workgroup that
     // the GPU holds (16 blocks of 300 lenses, six an item 49 us, one 17), and so many that the items stay fewer
     // than the tiles where they could pass 2^31.
-    uint64_t items = 0, taken = 0, inter = 0, tiles = 0, blocks = 0;
-    for (int32_t k = 0; k < n_jobs; ++k) {
-        tiles += (uint64_t)tile_count(&jobs[k], t);
-        blocks += (uint64_t)block_count(&jobs[k]);
-    }
-    if (tiles >= (uint64_t(1) << 31)) return fail(RS_ERANGE, "more than 2^31 ray tiles in one batch");
+    uint64_t items = 0, taken = 0, inter = 0;
     const int64_t least = tiles >= (uint64_t(1) << 29) ? rs::kWaves : 1;
     const uint64_t rays_per_tile = 64ull * (uint64_t)t.K1 * (uint64_t)rs::kWaves * (uint64_t)t.K2;
     start[0] = 0;
-    int32_t n_split = 0;
     for (int32_t k = 0; k < n_jobs; ++k) {
         const rs_job *job = &jobs[order[k]];
         uint32_t *counts = job->counts;
@@ -325,11 +330,10 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
         }
         int64_t nt = tile_count(job, t);
         uint64_t rays_per_item = rays_per_tile;
-        if (t.K1 == 1 && split_job(*job, blocks)) {
+        if (k < n_split) {
             const int64_t q = std::max<int64_t>(least, std::min<int64_t>({16, 2048 / std::max<int64_t>(job->n_lens, 1),
                                                                           (int64_t)(blocks / 6144)}));
             args[k].per_item = (uint32_t)q;
-            n_split = k + 1;   // (the jobs are in order of their lenses)
             nt = ((int64_t)args[k].n_blocks + q - 1) / q;
             rays_per_item = 256ull * (uint64_t)q;
         } else if (t.K1 == 1) {

@@ -33,18 +33,16 @@ struct RowGroups {
 // B lenses are staged by a wave at a time (private to it: the lens loop has no barrier).
 template <int B, int WV, int G = 1>
 struct SplitSmem {
-    static constexpr int kGroups = G;
     union {
         struct {
             float4 dy[WV][B * G];   // kJitter: the lens record; else x2 - x2_i of the four rows, of each row group
             float2 xm[WV][B];       // x1_i and the mass
         } st;
         double2 sum[WV][4][64];  // the waves' sums, after the lens loop
-        uint32_t win[kMaxWindow * kMaxWindow];
     };
     float4 rows[G];   // kGroupRows: x2 of the groups' rows
     uint32_t bad[64];
-    int cand[2][8];
+    int2 only[4];     // a row's only pixel and its rays there
     uint32_t lost;
 };
 
@@ -215,13 +213,13 @@ __device__ __forceinline__ void shoot_split(const Args &a, uint32_t c0, uint32_t
         wave_fence();
     }
 
-    // From here on thread (w, l), w < 4, owns the ray of row r0 + w of block l; further waves only help with
-    // the window.
+    // From here on thread (w, l), w < 4, owns the ray of row r0 + w of block l.
     const bool owner = wave < 4;
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 4; ++e) sm.sum[wave][e][lane] = make_double2(A1[e], A2[e]);
     if (tid < 64) sm.bad[tid] = 0u;
+    if (tid < 4) sm.only[tid].y = 0;
     if (tid == 0) sm.lost = 0u;
     __syncthreads();
     double B1 = 0.0, B2 = 0.0;
@@ -279,38 +277,36 @@ __device__ __forceinline__ void shoot_split(const Args &a, uint32_t c0, uint32_t
         a.ray_y[2 * ri + 1] = y2;
         a.ray_pix[ri] = kv;
     }
-    const int W = a.window;
-    int o1 = 0, o2 = 0;
-    if (W > 0) {
-        for (int b = tid; b < W * W; b += 64 * WV) sm.win[b] = 0u;
-        if (owner && (lane == 16 || lane == 48)) {
-            sm.cand[0][2 * wave + (lane >> 5)] = key >= 0 ? p1 : INT_MIN;
-            sm.cand[1][2 * wave + (lane >> 5)] = key >= 0 ? p2 : INT_MIN;
-        }
-        __syncthreads();
-        window_origin(sm.cand[0], sm.cand[1], lane, W, o1, o2);
-    }
+    // A row whose rays in the map are one run of one pixel leaves its count to the first wave, which adds equal
+    // pixels of the four rows up: where all rays meet a few pixels, additions to one cache line (10 ns each) bound
+    // the launch (2048^2 rays on one pixel, 100 lenses: 103 us, so 79; a batch of four such, 512 lenses: 2777, 1092).
+    // An LDS window of the map instead cost more than it saved on every map (100 lenses, 64 x 64: 105 us).
     uint32_t *part = a.partial + (size_t)(group & (kPartials - 1)) * (size_t)a.pstride;
     if (owner) {
         uint32_t cnt;
-        if (run_head(key, lane, cnt)) {
-            if (key >= 0) {
-                const int w1 = p1 - o1, w2 = p2 - o2;
-                if (W > 0 && (unsigned)w1 < (unsigned)W && (unsigned)w2 < (unsigned)W)
-                    atomicAdd(&sm.win[w2 * W + w1], cnt);
-                else
-                    atomicAdd(&part[key], cnt);
-            } else if (key == -1) {
-                atomicAdd(&sm.lost, cnt);
-            }
+        const bool head = run_head(key, lane, cnt), hit = head && key >= 0;
+        const unsigned long long hits = __ballot(hit);
+        const bool one = (hits & (hits - 1)) == 0;
+        if (hit) {
+            if (one) sm.only[wave] = make_int2(key, (int)cnt);
+            else atomicAdd(&part[key], cnt);
+        } else if (head && key == -1) {
+            atomicAdd(&sm.lost, cnt);
         }
     }
     __syncthreads();
-    if (W > 0) {
-        for (int b = tid; b < W * W; b += 64 * WV) {
-            const uint32_t v = sm.win[b];
-            if (v) atomicAdd(&part[(int64_t)(o2 + b / W) * a.mn1 + (o1 + b % W)], v);
+    if (tid < 4 && sm.only[tid].y > 0) {
+        const int k = sm.only[tid].x;
+        int cnt = 0;
+        bool first = true;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const int2 o = sm.only[w];
+            const bool same = o.x == k && o.y > 0;
+            cnt += same ? o.y : 0;
+            first = first && !(same && w < tid);
         }
+        if (first) atomicAdd(&part[k], (uint32_t)cnt);
     }
     if (tid == 0 && sm.lost) atomicAdd(lost_slot(a, group), (unsigned long long)sm.lost);
 }

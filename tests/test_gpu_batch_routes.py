@@ -8,11 +8,11 @@ pytestmark = pytest.mark.gpu
 
 # (lenses, columns, rows, jitter seed, moving) of each job; float32 run, staged tile, map window
 BATCHES = [
-    ([(255, 640, 1000, None, False), (256, 1000, 40, 3, False)], 0, 0, 0),           # under 4096 blocks, both kernels
-    ([(256, 700, 1600, None, True), (300, 64, 100, None, False)], 0, 0, 0),          # 4425: the second kernel alone
+    ([(255, 640, 790, None, False), (256, 1000, 14, 3, False)], 0, 0, 0),            # 2044 blocks: both kernels
+    ([(256, 640, 800, None, True), (300, 64, 151, None, False)], 0, 0, 0),           # 2049: both, by other jobs
     ([(511, 900, 1200, None, False), (512, 300, 333, 5, True), (0, 70, 50, None, False)], 0, 0, 0),   # both
-    ([(3, 130, 679, None, False), (0, 64, 4, None, False), (64, 5, 400, 7, False)], 0, 0, 0),         # 511 blocks
-    ([(3, 130, 679, None, False), (0, 64, 4, None, False), (64, 5, 404, 7, False)], 0, 0, 0),         # 512
+    ([(3, 130, 542, None, False), (0, 64, 4, None, False), (64, 5, 400, 7, False)], 0, 0, 0),         # 511 blocks
+    ([(3, 130, 542, None, False), (0, 64, 4, None, False), (64, 5, 404, 7, False)], 0, 0, 0),         # 512
     ([(40, 1024, 1024, None, False)] * 3 + [(2000, 200, 200, None, False)], 0, 0, -1),
     ([(40, 1024, 1024, None, False), (700, 512, 512, None, False)], 32, 512, 32),
     ([(100, 0, 10, None, False), (100, 200, 100, None, False), (1000, 10, 0, None, False)], 16, 0, 64),
