@@ -678,7 +678,7 @@ bool ray_block_supported(int K1, int K2)
 hipError_t launch_direct(const DirectArgs &a, int K1, int K2, int T, int LT, int64_t n_tiles, hipStream_t s)
 {
     if (n_tiles <= 0) return hipSuccess;
-    if (K1 == 1 && K2 == 4) {   // at most 64 lenses: the lens tile does not matter
+    if (K1 == 1 && K2 == 4) {   // few lenses, mostly: one lens tile
         if (T == 8) return launch_kt<1, 4, 8, 256>(a, n_tiles, s);
         if (T == 16) return launch_kt<1, 4, 16, 256>(a, n_tiles, s);
         if (T == 32) return launch_kt<1, 4, 32, 256>(a, n_tiles, s);

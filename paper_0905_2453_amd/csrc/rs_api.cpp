@@ -144,6 +144,21 @@ int64_t block_count(const rs_job *job)
     return ((job->grid.win_n[0] + 63) / 64) * ((kernel_rows(job->grid) + 3) / 4);
 }
 
+// Whether a window of `blocks` one-column blocks is shot with the lenses split over waves.  k_direct, whose
+// workgroup takes four times the rays, is the faster one on windows that fill the GPU with such workgroups while the
+// groups of 4 T lenses are fewer than the waves (us of k_split and k_direct: 640 x 512 rays, 64 lenses: 13.5, 16.8;
+// 4096 x 2048: 134, 108), and up to eight groups on windows that fill it many times over, unless the last group
+// holds a single run, which k_direct sums as a whole group (4096 x 2048: 96 lenses 149, 124; 100 154, 156; 128 171, 156;
+// 129 181, 188; 160 209, 188; 257 302, 322; but 1400^2: 96 lenses 45, 43; 100 46, 50; 160 61, 59; and with runs of 16
+// 200 lenses 257, 277).  With runs of 32 k_split spills registers: 2048^2 rays, 3000 lenses 1716, 1622; 1000^2 450, 480.
+bool takes_split(int64_t n_lens, int64_t blocks, int T)
+{
+    const int64_t groups = (n_lens + 4 * T - 1) / (4 * T), tail = n_lens - (groups - 1) * 4 * T;
+    if (groups <= 2) return blocks < 2048;
+    if (blocks < 16384) return true;
+    return T != 32 && !(T == 8 && groups <= 8 && (groups == 3 || tail > T));
+}
+
 // Device-side description of one job for a K1 x K2 ray block; counts go to `partial`.
 rs::DirectArgs make_args(const rs_job *job, const Tune &t, uint32_t *partial, int64_t pstride,
                          const rs_opts *opts)
@@ -261,9 +276,10 @@ struct PreparedBatch {
 // lenses 535, 429; 100 647, 657; 500 2118, 2228; 2000 7839, 8410; on 4 x 4 pixels, 4 x 2048^2 rays, 512 lenses 1348,
 // 1140, 1000 lenses 2190, 2196; one map of 1000^2 rays: 100 lenses 74, 52; 256 71, 66; 511 96, 112; of 512^2: 100
 // lenses 35, 34; 300 36, 50; of 256^2: 64 lenses 18, 27.
-bool split_job(const rs_job &j, uint64_t blocks)
+bool split_job(const rs_job &j, uint64_t blocks, int T)
 {
     const bool few_pixels = (int64_t)j.map.n[0] * j.map.n[1] <= 1024;
+    if (T == 32 && blocks >= 16384) return false;   // as takes_split
     return j.n_lens >= (few_pixels ? 1024 : 512) || blocks < 8 * (uint64_t)std::max<int64_t>(64, j.n_lens);
 }
 
@@ -297,7 +313,7 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     if (tiles >= (uint64_t(1) << 31)) return fail(RS_ERANGE, "more than 2^31 ray tiles in one batch");
     std::vector<int32_t> order(n_jobs);
     std::iota(order.begin(), order.end(), 0);
-    auto split = [&](int32_t k) { return t.K1 == 1 && split_job(jobs[k], blocks); };
+    auto split = [&](int32_t k) { return t.K1 == 1 && split_job(jobs[k], blocks, t.run()); };
     const auto whole = std::stable_partition(order.begin(), order.end(), split);
     auto costlier = [&](int32_t a, int32_t b) { return jobs[a].n_lens > jobs[b].n_lens; };
     std::stable_sort(order.begin(), whole, costlier);
@@ -593,11 +609,7 @@ int shoot_with_partials(const rs_job *job, const Tune &t, uint32_t *part, hipStr
     use_partials(a, part);
     hipError_t e = rs::launch_zero(part, partial_words(job), s);
     if (e != hipSuccess) return dev_fail(e, "zero partial maps");
-    // One-column blocks split the lenses over waves; with one or two groups of lenses most waves would have
-    // none, and on large windows k_direct, whose workgroup takes four times the rays, is the faster one
-    // (4096 x 2048 rays, 64 lenses: 108 us against 134, 101 lenses 180 against 163; 640 x 512 rays, 64
-    // lenses: 16.8 against 13.5).
-    if (t.K1 == 1 && (job->n_lens > 64 || a.n_blocks < 2048)) e = rs::launch_split(a, t.run(), t.LT, s);
+    if (t.K1 == 1 && takes_split(job->n_lens, a.n_blocks, t.run())) e = rs::launch_split(a, t.run(), t.LT, s);
     else e = rs::launch_direct(a, t.K1, t.K2, t.run(), t.LT, tile_count(job, t), s);
     if (e != hipSuccess) return dev_fail(e, "direct-sum launch");
     e = rs::launch_reduce(part, bins, pstride, job->counts, reinterpret_cast<unsigned long long *>(job->n_lost), s);
