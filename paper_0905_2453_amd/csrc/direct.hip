@@ -692,7 +692,7 @@ hipError_t launch_direct(const DirectArgs &a, int K1, int K2, int T, int LT, int
     return hipErrorInvalidValue;
 }
 
-// several-column blocks (one-column ones: split.hip, and k_batched<1, 4> for a batch's jobs of few lenses)
+// several-column blocks (one-column ones: split.hip, and <1, 4> below for batches and zooms of few lenses)
 #define RS_BLOCK_SWITCH(FN, ...)                                              \
     if (K1 == 2 && K2 == 2) return FN<2, 2>(__VA_ARGS__);                     \
     if (K1 == 2 && K2 == 4) return FN<2, 4>(__VA_ARGS__);                     \
@@ -711,6 +711,7 @@ hipError_t launch_direct_cells(const DirectArgs &a, int K1, int K2, int T, int L
                                int64_t max_groups, hipStream_t s)
 {
     if (max_groups <= 0) return hipSuccess;
+    if (K1 == 1 && K2 == 4) return launch_c<1, 4>(a, T, LT, cb, max_groups, s);
     RS_BLOCK_SWITCH(launch_c, a, T, LT, cb, max_groups, s)
     return hipErrorInvalidValue;
 }

@@ -742,6 +742,11 @@ int rs_magnification(const uint32_t *counts, const rs_raygrid *grid, const rs_ma
 
 // ---------------------------------------------------------------- zoom
 
+// Lenses from which a zoom's one-column cells are listed by row and shot by k_split_cells.  Fewer go to k_direct_cells,
+// whose workgroup takes four times the rays and needs no rows (us of a zoom, 4096^2 rays: 10 lenses 108, 66; 300 lenses 487,
+// 491, a small area of them 144, 129; 500 lenses 710, 842).
+constexpr int64_t kZoomSplit = 384;
+
 struct ZoomLayout {
     int64_t c1 = 0, c2 = 0, ncx = 0, ncy = 0, cells = 0, sx = 0, S = 0;
     int levels = rs::kZoomLevels;
@@ -1099,10 +1104,11 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     const rs_raygrid &g = job->grid;
     const bool empty = g.win_n[0] == 0 || g.win_n[1] == 0;
     uint32_t *part = reinterpret_cast<uint32_t *>(base + L.part_off);
+    const bool split = t.K1 == 1 && job->n_lens >= kZoomSplit;
     // (the list's and the partial maps' parts of the workspace are whole 16-byte words)
     rs::ZoomInit zi{stats, (uint32_t)L.cells, (uint32_t)L.S, (uint32_t)(t.K1 * t.K2),
                     reinterpret_cast<uint4 *>(base + L.list_off[L.levels - 1]), reinterpret_cast<uint4 *>(part),
-                    empty || t.K1 != 1 ? 0 : (L.cells + 3) / 4, empty ? 0 : partial_words(job) / 4};
+                    empty || !split ? 0 : (L.cells + 3) / 4, empty ? 0 : partial_words(job) / 4};
     hipError_t e = rs::launch_zoom_init(zi, s);
     if (e != hipSuccess) return dev_fail(e, "zoom reset");
     if (empty) return RS_OK;
@@ -1110,6 +1116,7 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     const int64_t pstride = partial_stride(job);
     const int64_t bins = (int64_t)job->map.n[0] * job->map.n[1];
     rs::DirectArgs a = make_args(job, t, part, pstride, opts);
+    if (t.K1 == 1 && !split && t.W < 0) a.window = 64;
     use_partials(a, part);
 
     rs::ZoomArgs z{};
@@ -1153,7 +1160,7 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     z.time = a.time;
     z.list = z.lists[L.levels - 1];
     z.stats = stats;
-    z.flags = t.K1 == 1;
+    z.flags = split;
 
     rs::CellBlocks cb{};
     cb.list = z.list;
@@ -1173,7 +1180,7 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     e = rs::launch_zoom_mark(z, s);
     if (e == hipSuccess && z.flags) e = rs::launch_zoom_rows(cb, z.list, s);
     if (e != hipSuccess) return dev_fail(e, "zoom culling launch");
-    if (t.K1 == 1) e = rs::launch_split_cells(a, t.run(), t.LT, cb, s);
+    if (split) e = rs::launch_split_cells(a, t.run(), t.LT, cb, s);
     else e = rs::launch_direct_cells(a, t.K1, t.K2, t.run(), t.LT, cb, max_groups, s);
     if (e != hipSuccess) return dev_fail(e, "zoom direct-sum launch");
     e = rs::launch_reduce(part, bins, pstride, job->counts, reinterpret_cast<unsigned long long *>(job->n_lost), s);

@@ -24,7 +24,6 @@ namespace rs {
 namespace {
 
 constexpr int kZoomRun = 16;     // float32 run length before the FP64 combine
-constexpr int kZoomWaves = 8;    // waves of a workgroup, each with every kZoomWaves-th chunk of 64 lenses
 constexpr int kZoomSums = 8;
 
 __device__ __forceinline__ float4 zoom_pad_lens()
@@ -81,8 +80,8 @@ __device__ __forceinline__ void zoom_run(const float4 *L, float cf1, float cf2, 
 // A child's rectangle lies inside its parent's, so a cell whose image can meet the map is kept
 // at every level above it.
 //
-// Persistent: a workgroup takes 64 / ks cells at a time from the level's counter.  Its waves split the lenses
-// (wave w sums the chunks of 64 lenses w, w + 8, ..., staged privately), and ks (1, 2 or 4) consecutive
+// Persistent: a workgroup takes 64 / ks cells at a time from the level's counter.  Its WV waves split the lenses
+// (wave w sums the chunks of 64 lenses w, w + WV, ..., staged privately), and ks (1, 2 or 4) consecutive
 // lanes share a cell, each summing every ks-th run of the chunks; the partial sums meet in a fixed butterfly
 // and then in LDS in wave order.  A level has few cells (15 000 to 140 000 on the benchmark's zoom), so a lane
 // that sums a cell alone, or a sixteenth of it, leaves most wave slots empty (1.8 waves per SIMD on average).  The
@@ -91,30 +90,37 @@ __device__ __forceinline__ void zoom_run(const float4 *L, float cf1, float cf2, 
 // different runs at once: with a place skipped after each run these lie on different banks, and with eight waves two
 // workgroups fit a compute unit, one's merge under the other's sums: 14.3 ms (runs on the same banks 16.1, the skip
 // alone 15.1; 30 000 lenses: 2.45, 2.17, both 2.02).
-__global__ void __launch_bounds__(64 * kZoomWaves, 4) k_zoom_mark(const ZoomArgs z, int level, int ks)
+// Fields of fewer chunks than eight take as many waves; their items are cheap, so workgroups step through them without
+// the counter (a take costs about 12 ns, with 4096 workgroups 50 us a level), and ks follows the level's real number of
+// cells (`lanes` of them or more: 1; 64 lenses, 0.02 of 4096^2 rays' span: 76 us from the host's estimate, 69).
+template <int WV>
+__global__ void __launch_bounds__(64 * WV, 4) k_zoom_mark(const ZoomArgs z, int level, int ks, int lanes)
 {
     __shared__ union {
-        float4 lens[kZoomWaves][64 + 64 / kZoomRun];   // a place is skipped after each run
-        double sum[kZoomWaves][kZoomSums][64];
+        float4 lens[WV][64 + 64 / kZoomRun];   // a place is skipped after each run
+        double sum[WV][kZoomSums][64];
     } sm;
     __shared__ uint32_t s_inside[64];
     __shared__ uint32_t s_item;
+    constexpr bool QUEUE = WV == 8;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int part = lane & (ks - 1);
     const int64_t P = z.P, PP = z.P * z.P;
     const int64_t cw1 = z.lcw1[level], cw2 = z.lcw2[level];
     const int64_t n_items = level == 0 ? z.lnx[0] * z.lny[0] : (int64_t)z.stats[4 + level - 1] * PP;
+    if (!QUEUE)
+        for (ks = 1; ks < 4 && n_items * ks < lanes;) ks <<= 1;
+    const int part = lane & (ks - 1);
     const int64_t n_chunks = (z.n_lens + 63) / 64;
     auto fetch = [&](int64_t c) -> float4 {
         const int64_t i = c * 64 + lane;
         return i < z.n_lens ? moved_lens(z.lenses[i], z.vel, i, z.time) : zoom_pad_lens();
     };
-    for (;;) {
+    for (int64_t item = blockIdx.x;; item += gridDim.x) {
         __syncthreads();   // the last item's sums are read
-        if (tid == 0) s_item = atomicAdd(&z.stats[kZoomQueue + level], 1u);
+        if (QUEUE && tid == 0) s_item = atomicAdd(&z.stats[kZoomQueue + level], 1u);
         if (tid < 64) s_inside[tid] = 0u;
         __syncthreads();
-        const int64_t first = (int64_t)s_item * (64 / ks);
+        const int64_t first = (QUEUE ? (int64_t)s_item : item) * (64 / ks);
         if (first >= n_items) break;
         const int64_t t_id = first + lane / ks;
         int64_t cx = 0, cy = 0, idx = 0;
@@ -156,10 +162,10 @@ __global__ void __launch_bounds__(64 * kZoomWaves, 4) k_zoom_mark(const ZoomArgs
         bool inside = false;
         float4 nxt = zoom_pad_lens();
         if (wave < n_chunks) nxt = fetch(wave);
-        for (int64_t c = wave; c < n_chunks; c += kZoomWaves) {
+        for (int64_t c = wave; c < n_chunks; c += WV) {
             sm.lens[wave][lane + lane / kZoomRun] = nxt;
             zoom_wave_fence();
-            if (c + kZoomWaves < n_chunks) nxt = fetch(c + kZoomWaves);
+            if (c + WV < n_chunks) nxt = fetch(c + WV);
             for (int r = part * kZoomRun; r < 64; r += ks * kZoomRun) {
                 const float4 *L = &sm.lens[wave][r + r / kZoomRun];
                 float s1, s2, sd, so, sc, sp, sq, rmin;
@@ -206,8 +212,8 @@ __global__ void __launch_bounds__(64 * kZoomWaves, 4) k_zoom_mark(const ZoomArgs
             D2 += __shfl_xor(D2, o, 64);
             nearsum += __shfl_xor(nearsum, o, 64);
         }
-        __syncthreads();   // every wave is done with its staged lenses
-        {
+        if constexpr (WV > 1) {
+            __syncthreads();   // every wave is done with its staged lenses
             const double v[kZoomSums] = {A1, A2, Jd, Jo, C3, P1, D2, nearsum};
 #pragma unroll
             for (int k = 0; k < kZoomSums; ++k) sm.sum[wave][k][lane] = v[k];
@@ -215,18 +221,20 @@ __global__ void __launch_bounds__(64 * kZoomWaves, 4) k_zoom_mark(const ZoomArgs
         if (inside) s_inside[lane - part] = 1u;
         __syncthreads();
         if (wave == 0) {
-            double v[kZoomSums] = {};
-            for (int w = 0; w < kZoomWaves; ++w)
+            if constexpr (WV > 1) {
+                double v[kZoomSums] = {};
+                for (int w = 0; w < WV; ++w)
 #pragma unroll
-                for (int k = 0; k < kZoomSums; ++k) v[k] += sm.sum[w][k][lane];
-            A1 = v[0];
-            A2 = v[1];
-            Jd = v[2];
-            Jo = v[3];
-            C3 = v[4];
-            P1 = v[5];
-            D2 = v[6];
-            nearsum = v[7];
+                    for (int k = 0; k < kZoomSums; ++k) v[k] += sm.sum[w][k][lane];
+                A1 = v[0];
+                A2 = v[1];
+                Jd = v[2];
+                Jo = v[3];
+                C3 = v[4];
+                P1 = v[5];
+                D2 = v[6];
+                nearsum = v[7];
+            }
             inside = s_inside[lane - part] != 0u;
             double h1, h2;
             geometry(cf1, cf2, h1, h2);
@@ -343,15 +351,17 @@ hipError_t launch_zoom_rows(const CellBlocks &cb, uint32_t *list, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_zoom_mark(const ZoomArgs &z, hipStream_t s)
+template <int WV>
+hipError_t launch_mark(const ZoomArgs &z, hipStream_t s)
 {
     int64_t items = z.lnx[0] * z.lny[0];
     if (items <= 0) return hipSuccess;
     int occ = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_zoom_mark, 64 * kZoomWaves, 0) != hipSuccess) occ = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_zoom_mark<WV>, 64 * WV, 0) != hipSuccess) occ = 1;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 256;
+    const int lanes = 64 * 4 / WV * cus;
     for (int l = 0; l < z.levels; ++l) {
         // level l > 0 runs over at most every child of every cell of level l - 1.  Lanes per cell: enough
         // to give two workgroups per compute unit for the expected work (every cell at level 0, the children
@@ -360,13 +370,24 @@ hipError_t launch_zoom_mark(const ZoomArgs &z, hipStream_t s)
         const int64_t expect = l == 0 ? items : std::max<int64_t>(1, items / 3);
         int ks = 1;
         while (ks < 4 && expect * ks < int64_t(64) * 2 * cus) ks <<= 1;
-        const int64_t per_block = 64 / ks;
+        const int64_t per_block = WV < 8 ? 16 : 64 / ks;
         const int64_t grid = std::min<int64_t>((items + per_block - 1) / per_block, (int64_t)std::max(1, occ) * cus);
-        hipLaunchKernelGGL(k_zoom_mark, dim3((unsigned)grid), dim3(64 * kZoomWaves), 0, s, z, l, ks);
+        hipLaunchKernelGGL(k_zoom_mark<WV>, dim3((unsigned)grid), dim3(64 * WV), 0, s, z, l, ks, lanes);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t launch_zoom_mark(const ZoomArgs &z, hipStream_t s)
+{
+    // As many waves as there are chunks of 64 lenses, up to eight: waves without a chunk only wait and merge, and one
+    // wave with two chunks takes longer (128 lenses, 4096^2 rays: 107 us a zoom with one wave, 81 with two, 127 with
+    // eight).
+    if (z.n_lens <= 64) return launch_mark<1>(z, s);
+    if (z.n_lens <= 128) return launch_mark<2>(z, s);
+    if (z.n_lens <= 256) return launch_mark<4>(z, s);
+    return launch_mark<8>(z, s);
 }
 
 }  // namespace rs
