@@ -1243,8 +1243,8 @@ __global__ void k_cells_sort(const CellArgs g)
 // ---------------------------------------------------------------- eval: surrogate
 
 // `splits` workgroups per fit tile, workgroup q taking passes q, q + splits, ... of the tile's
-// rays (every ray is computed the same way whatever the split).  A lane holds four rays of a column
-// (rows 4 r .. 4 r + 3 of the tile), so a pass shoots 1024 rays:
+// rays (every ray is computed the same way whatever the split).  A lane holds ROWS rays of a column
+// (four: rows 4 r .. 4 r + 3 of the tile, a pass shoots 1024 rays; or one, see launch_surrogate):
 //   far field: affine base plus the network (on MFMA, 32 rays at a time, a lane pair per ray; the
 //     coordinates and outputs change lanes through LDS);
 //   near field: summed exactly, one reciprocal per ray and lens, over the candidate lenses of the cells
@@ -1253,7 +1253,7 @@ __global__ void k_cells_sort(const CellArgs g)
 //
 // Bound: the issue of its VALU instructions (a reciprocal counts five), about half of them the near field.  Of the
 // candidates a third are out of reach (the corners of the cells' box): staging keeps only the near ones of
-// a run, filled up to a multiple of four with lenses without mass, which add exact zeros, so a run's sum is that
+// a run, filled up to an even number with a lens without mass, which add exact zeros, so a run's sum is that
 // of all sixteen.  Four rays per lane share x1 - x1_i and its square (cell-centred rays) and each LDS read.
 // 4096^2 rays in 64^2 tiles, about 200 near lenses: 1.24 ms (40 us less with the network's
 // priority below); one ray per lane pair, all candidates: 2.03.
@@ -1264,14 +1264,14 @@ struct NearStage {
     uint16_t start[kNearCap / kNearRun + 2];  // first lens of each run; the entry after the last ends it
 };
 
-template <bool DUMP, bool JIT>
+template <bool DUMP, bool JIT, int ROWS>
 __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const CellArgs g, int splits)
 {
-    constexpr int CAP = kNearCap, T = kNearRun, NX = JIT ? 4 : 1;
+    constexpr int CAP = kNearCap, T = kNearRun, NX = JIT ? ROWS : 1;
     __shared__ __attribute__((aligned(16))) uint16_t Wbf[kNParamsPad];
     __shared__ __attribute__((aligned(16))) float sbias[130];
     __shared__ NearStage s_near;
-    __shared__ float2 s_net[4][4][64];   // per wave and row: the rays' tile coordinates, then the network outputs
+    __shared__ float2 s_net[4][ROWS][64];   // per wave and row: the rays' tile coordinates, then the network outputs
     __shared__ __attribute__((aligned(16))) uint32_t s_zero[4];
     __shared__ int s_cells[4];
     __shared__ int2 s_rows[64];
@@ -1399,15 +1399,16 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
     if (n_batches == 1) stage(0);
     __syncthreads();
 
-    const int quads = n[0] * ((n[1] + 3) / 4);   // blocks of four rays of a column
-    const int passes = (quads + 255) / 256;
+    const int blocks = n[0] * ((n[1] + ROWS - 1) / ROWS);   // of ROWS rays of a column
+    const int passes = (blocks + 255) / 256;
     for (int ps = (int)split; ps < passes; ps += splits) {
         const int qi = 256 * ps + 64 * wave + lane;
-        const int ix = qi % n[0], iy = qi / n[0] * 4;
+        const int ix = qi % n[0], iy = qi / n[0] * ROWS;
+        const int rows = qi < blocks ? min(ROWS, n[1] - iy) : 0;   // the lane's rays
         const int64_t g1 = i0[0] + ix;
-        float x1[NX], x2[4];
+        float x1[NX], x2[ROWS];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < ROWS; ++e) {
             const int64_t g2 = i0[1] + iy + e, rg = g2 * f.gn1 + g1;
             if (e < NX) x1[e] = ray_coord(f.glo1, f.gt1, g1, JIT ? jitter_u(f.jkey1, rg) : 0.5);
             x2[e] = ray_coord(f.glo2, f.gt2, g2, JIT ? jitter_u(f.jkey2, rg) : 0.5);
@@ -1417,7 +1418,7 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
         if (!f.affine_only) {
             float u1 = 0.f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < ROWS; ++e) {
                 if (e < NX) u1 = (float)(((double)x1[e] - c[0]) / hw[0]);
                 net[e][lane] = make_float2(u1, (float)(((double)x2[e] - c[1]) / hw[1]));
             }
@@ -1427,7 +1428,8 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
             // it; 3000 x 1000 in 100^2: 0.85, 0.81)
             __builtin_amdgcn_s_setprio(1);
 #pragma unroll 1
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < 2 * ROWS; ++k) {
+                if (!(uint32_t)(__ballot((k >> 1) < rows) >> (32 * (k & 1)))) continue;   // none of the 32 is a ray
                 float2 *ray = &net[k >> 1][32 * (k & 1) + col];
                 const float2 u = *ray;
                 uint32_t phi4[4];
@@ -1441,19 +1443,20 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
             __builtin_amdgcn_s_setprio(0);
         }
         // near field
-        double A1[4] = {}, A2[4] = {};
+        double A1[ROWS] = {}, A2[ROWS] = {};
+        const bool any = __any(rows > 0);
         for (int b = 0; b < n_batches; ++b) {
             if (n_batches > 1) {
                 __syncthreads();
                 stage(b);
                 __syncthreads();
             }
-            const int runs = (min(CAP, n_cand - b * CAP) + T - 1) / T;
+            const int runs = any ? (min(CAP, n_cand - b * CAP) + T - 1) / T : 0;
             int at = 0;
             for (int r = 0; r < runs; ++r) {
                 const int end = __builtin_amdgcn_readfirstlane((int)s_near.start[r + 1]);
                 if (at == end) continue;      // no near lens: the run's sum is zero
-                float s1[4] = {}, s2[4] = {};
+                float s1[ROWS] = {}, s2[ROWS] = {};
                 auto add = [&](int k) __attribute__((always_inline)) {
                     const float4 l = s_near.lens[k];
                     float dx[NX], dx2[NX];
@@ -1463,7 +1466,7 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
                         dx2[e] = dx[e] * dx[e];
                     }
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
+                    for (int e = 0; e < ROWS; ++e) {
                         const float dy = x2[e] - l.y;
                         const float d = l.z * __builtin_amdgcn_rcpf(fmaf(dy, dy, dx2[JIT ? e : 0]));
                         s1[e] = fmaf(d, dx[JIT ? e : 0], s1[e]);
@@ -1480,7 +1483,7 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
                     at += 2;
                 }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
+                for (int e = 0; e < ROWS; ++e) {
                     A1[e] += (double)s1[e];
                     A2[e] += (double)s2[e];
                 }
@@ -1488,7 +1491,7 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
         }
         const double a01 = ab[0], a02 = ab[1], j11 = ab[2], j12 = ab[3], j22 = ab[4], st = hd[9];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < ROWS; ++e) {
             const float2 o = f.affine_only ? make_float2(0.f, 0.f) : net[e][lane];
             const double X1 = (double)x1[JIT ? e : 0], X2 = (double)x2[e];
             const double d1 = X1 - c[0], d2 = X2 - c[1];
@@ -1497,7 +1500,7 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
             const double y1 = f.lam1 * X1 - (F1 + A1[e] * kRcpBiasComp);
             const double y2 = f.lam2 * X2 - (F2 + A2[e] * kRcpBiasComp);
             int key = -2;
-            if (qi < quads && iy + e < n[1]) {
+            if (e < rows) {
                 const double p1 = floor((y1 - f.mlo1) * f.ms1), p2 = floor((y2 - f.mlo2) * f.ms2);
                 key = (p1 >= 0.0 && p1 < (double)f.mn1 && p2 >= 0.0 && p2 < (double)f.mn2) ? (int)p2 * f.mn1 + (int)p1 : -1;
                 if (DUMP) {
@@ -1636,6 +1639,32 @@ hipError_t launch_ff_fit(const FarArgs &f, uint64_t hash, hipStream_t s)
     return hipGetLastError();
 }
 
+template <bool JIT, int ROWS>
+hipError_t launch_surrogate_rows(const FarArgs &f, const CellArgs &g, uint32_t grid, hipStream_t s)
+{
+    // few tiles: their rays split over so many workgroups that about 4096 run, each with at least one pass (a
+    // workgroup's staging costs a tenth of a pass: 4 tiles of 1024^2 rays over 1024 workgroups each 0.89 ms, over
+    // 32 2.4, over 8 9.4; 256 tiles of 256^2 over 16 1.57 ms, over 8 1.64)
+    const int64_t passes = ((int64_t)f.TX * ((f.TY + ROWS - 1) / ROWS) + 255) / 256;
+    const int splits = (int)std::max<int64_t>(1, std::min<int64_t>(passes, (4096 + grid - 1) / grid));
+    const dim3 gr(grid * (uint32_t)splits), blk(256);
+    if (f.ray_y) hipLaunchKernelGGL((k_surrogate<true, JIT, ROWS>), gr, blk, 0, s, f, g, splits);
+    else hipLaunchKernelGGL((k_surrogate<false, JIT, ROWS>), gr, blk, 0, s, f, g, splits);
+    return hipGetLastError();
+}
+
+template <bool JIT>
+hipError_t launch_surrogate(const FarArgs &f, const CellArgs &g, uint32_t grid, hipStream_t s)
+{
+    // Four rays a lane share their lens and network reads, but need tiles that fill a pass (at least half as many rays in
+    // it as in passes of one ray a lane) and passes enough for the GPU.  us of an evaluation with four rays and with
+    // one: 1500 x 700 rays in tiles of 64^2 162, 164; 32^2 163, 178; 64 x 5 209, 212; 16^2 225, 191; 8^2 466, 310; 64 x 1 405, 311;
+    // in 64^2 tiles: 500^2 rays (256 passes) 110, 97; 700^2 (484) 120, 119; 1000^2 (1024) 144, 154; 2000^2 298, 322.
+    const int64_t four = ((int64_t)f.TX * ((f.TY + 3) / 4) + 255) / 256, one = ((int64_t)f.TX * f.TY + 255) / 256;
+    return one >= 2 * four && grid * four >= 768 ? launch_surrogate_rows<JIT, 4>(f, g, grid, s)
+                                                 : launch_surrogate_rows<JIT, 1>(f, g, grid, s);
+}
+
 hipError_t launch_ff_eval(const FarArgs &f, const CellArgs &g, hipStream_t s)
 {
     hipError_t e;
@@ -1653,20 +1682,7 @@ hipError_t launch_ff_eval(const FarArgs &f, const CellArgs &g, hipStream_t s)
     if (f.affine) {
         if ((e = launch_affine(f, grid, s)) != hipSuccess) return e;
     }
-    // few tiles: their rays split over so many workgroups that about 4096 run, each with at least one pass (a
-    // workgroup's staging costs a tenth of a pass: 4 tiles of 1024^2 rays over 1024 workgroups each 0.89 ms, over
-    // 32 2.4, over 8 9.4; 256 tiles of 256^2 over 16 1.57 ms, over 8 1.64)
-    const int64_t passes = ((int64_t)f.TX * ((f.TY + 3) / 4) + 255) / 256;
-    const int splits = (int)std::max<int64_t>(1, std::min<int64_t>(passes, (4096 + grid - 1) / grid));
-    const dim3 gr(grid * (uint32_t)splits), blk(256);
-    if (f.jitter) {
-        if (f.ray_y) hipLaunchKernelGGL((k_surrogate<true, true>), gr, blk, 0, s, f, g, splits);
-        else hipLaunchKernelGGL((k_surrogate<false, true>), gr, blk, 0, s, f, g, splits);
-    } else {
-        if (f.ray_y) hipLaunchKernelGGL((k_surrogate<true, false>), gr, blk, 0, s, f, g, splits);
-        else hipLaunchKernelGGL((k_surrogate<false, false>), gr, blk, 0, s, f, g, splits);
-    }
-    return hipGetLastError();
+    return f.jitter ? launch_surrogate<true>(f, g, grid, s) : launch_surrogate<false>(f, g, grid, s);
 }
 
 }  // namespace rs

@@ -1,0 +1,62 @@
+"""GPU check that a closure's tile is evaluated alike in the whole window and in a list of a few tiles, whatever the
+layouts that the two calls choose (rays per lane, workgroups per tile, workgroups that share a moving tile's lenses):
+every ray's source position bit for bit, in whole tiles and the ragged ones of the window's edges, network on.
+"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("moving,jitter,tile,rays", [
+    (False, None, (64, 64), (1000, 900)),      # 240 tiles: four rays a lane, listed ones one
+    (False, 5, (64, 64), (1000, 900)),
+    (False, None, (33, 70), (1990, 901)),      # 793 tiles, 7.5 passes of one ray
+    (False, 3, (16, 9), (700, 500)),           # one ray a lane in both
+])
+def test_listed_tiles_equal_whole(moving, jitter, tile, rays):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_0905_2453_amd as P
+    P.lib()
+    print(f"tiles {tile} of {rays} rays, jitter {jitter}, moving {moving}", flush=True)
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(rays[0])
+    lenses = torch.rand((6000, 4), device=dev, generator=g)
+    lenses[:, :2] = 60.0 * lenses[:, :2] - 30.0
+    vel = 0.1 * torch.randn((6000, 2), device=dev, generator=g)
+    samples = 2.0 * torch.rand((1024, 2), device=dev, generator=g) - 1.0
+    init = 0.1 * (torch.rand(5378, device=dev, generator=g) - 0.5)
+    args = (lenses, 0.05, 0.1, (-9.0, -8.0), (9.0, 8.5), rays, (-4.0, -4.0), (4.0, 4.0), (60, 50))
+    u8 = dict(dtype=torch.uint8, device=dev)
+    tiles = -(-rays[0] // tile[0]) * -(-rays[1] // tile[1])
+    listed = sorted({0, 7, tiles // 2, tiles - 2, tiles - 1})
+    model, got = None, []
+    for subset in (None, listed, listed[2:3]):
+        counts = torch.zeros((50, 60), dtype=torch.int32, device=dev)
+        lost = torch.zeros(1, dtype=torch.int64, device=dev)
+        static = P.make_job(*args, counts, lost, jitter_seed=jitter)
+        job = P.make_job(*args, counts, lost, jitter_seed=jitter, velocities=vel, time=0.6) if moving else static
+        cfg = P.ff_config(samples, init, tile_rays=tile, r_near=2.0, steps=8, batch=256,
+                          eval_tiles=torch.tensor(subset, dtype=torch.int32, device=dev) if subset else None)
+        if model is None:
+            model = torch.empty(P.farfield_model_bytes(static, cfg), **u8)
+            P.farfield_fit(static, cfg, model, torch.empty(P.farfield_fit_workspace_bytes(static, cfg), **u8))
+        y = torch.full((rays[1], rays[0], 2), float("nan"), dtype=torch.float64, device=dev)
+        pix = torch.full((rays[1], rays[0]), -7, dtype=torch.int32, device=dev)
+        o = P.Opts()
+        o.ray_y, o.ray_pix = y.data_ptr(), pix.data_ptr()
+        P.farfield_eval(job, cfg, model, torch.empty(P.farfield_eval_workspace_bytes(job, cfg), **u8), o)
+        assert torch.equal(counts.view(-1).cpu(), torch.bincount(pix[pix >= 0].long(), minlength=3000).int().cpu())
+        assert int(lost.item()) == int((pix == -1).sum())
+        got.append((y, pix))
+    assert int((got[0][1] == -7).sum()) == 0
+    across = -(-rays[0] // tile[0])
+    for (y, pix), subset in zip(got[1:], (listed, listed[2:3])):
+        shot = torch.zeros_like(pix, dtype=torch.bool)
+        for t in subset:
+            ty, tx = t // across * tile[1], t % across * tile[0]
+            shot[ty:ty + tile[1], tx:tx + tile[0]] = True
+        assert torch.equal(pix != -7, shot)
+        assert torch.equal(pix[shot], got[0][1][shot])
+        assert torch.equal(y[shot].view(torch.int64), got[0][0][shot].view(torch.int64))
