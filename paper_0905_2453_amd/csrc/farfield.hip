@@ -299,8 +299,8 @@ __device__ __forceinline__ void forward32(const uint16_t *Wbf, const float *sbia
 
 // alpha_far(c) and its Jacobian over the far set of each tile, FP64; a workgroup takes NT
 // consecutive tiles (of the tile list when one is given), so every lens record it loads serves
-// all of them (NT = 4 when there are enough tiles to fill the GPU, else 1).  Each tile's sums are those of a workgroup of its own: thread t
-// takes lenses t, t + 256, ... in order, then a fixed tree adds the 256 partial sums.  At fit
+// all of them (NT = 4 when there are enough tiles to fill the GPU, else 1).  Unless SPLIT, each tile's sums are those
+// of a workgroup of its own: thread t takes lenses t, t + 256, ... in order, then a fixed tree adds the 256 partial sums.  At fit
 // time the result goes into the model's tile header.  For a moving field (eval with
 // velocities) the far set is still the one chosen by the fit-time positions, each far lens
 // enters at its position at f.time, and the result goes to f.affine (only the evaluated tiles).
@@ -1577,11 +1577,12 @@ hipError_t launch_lens_checksum(const float4 *lenses, int64_t n, unsigned long l
 }
 
 // affine bases of `count` tiles: four per workgroup once there are at least 8192 (2048 workgroups), else one
-// per workgroup (the sums are the same either way), and below 1024 tiles of a moving field so many workgroups
-// per tile that about kAffineParts run
+// per workgroup (the sums are the same either way), and for a moving field in fewer than 1024 tiles so many workgroups
+// per tile that about kAffineParts run for them all (by the model's tiles, not by the listed ones: the number decides
+// the order of a tile's sums, and a listed tile is to get the base that it gets in the whole window)
 hipError_t launch_affine(const FarArgs &f, int64_t count, hipStream_t s)
 {
-    const int parts = f.affine ? (int)std::min<int64_t>({64, kAffineParts / count, (f.n_lens + 255) / 256}) : 1;
+    const int parts = f.affine ? (int)std::min<int64_t>({64, kAffineParts / f.n_tiles, (f.n_lens + 255) / 256}) : 1;
     if (count >= 8192) {
         hipLaunchKernelGGL((k_ff_affine<4, false>), dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s, f);
     } else if (parts < 2) {

@@ -12,6 +12,9 @@ pytestmark = pytest.mark.gpu
     (False, 5, (64, 64), (1000, 900)),
     (False, None, (33, 70), (1990, 901)),      # 793 tiles, 7.5 passes of one ray
     (False, 3, (16, 9), (700, 500)),           # one ray a lane in both
+    (True, None, (64, 64), (1000, 900)),       # a moving field's affine bases: 8 workgroups a tile
+    (True, 4, (100, 100), (310, 205)),         # 24, all that the lenses fill
+    (True, None, (16, 9), (700, 500)),         # one
 ])
 def test_listed_tiles_equal_whole(moving, jitter, tile, rays):
     import torch
