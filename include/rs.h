@@ -233,8 +233,9 @@ int rs_shoot_batched(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t
  * Pick the block shape and map window for a batch by timing candidates (1x4, 2x4, 4x4, 2x8 ray
  * blocks x 32/64 windows) on the batch's costliest tiles, with counts sent to the workspace's
  * scratch map (the jobs' maps are not touched).  *best supplies fp32_run and lens_tile and
- * receives block_cols, block_rows, lens_tile and map_window.  If cache_path (nullable) holds
- * an entry for this device and batch class (median lens count, ray count and map size, in
+ * receives block_cols, block_rows, lens_tile and map_window (which of the 1x4 kernels only that of
+ * jobs of few lenses has).  If cache_path (nullable) holds an entry for this device, this
+ * generation of kernels and batch class (median lens count, ray count and map size, in
  * powers of two) it is used without timing; otherwise the result is appended to the file.
  * Synchronises the stream.
  */

@@ -475,7 +475,8 @@ std::string tune_key(const rs_job *jobs, int32_t n_jobs)
         return (long)std::lround(v[v.size() / 2]);
     };
     std::ostringstream o;
-    o << arch << "|lens2^" << med(nl) << "|rays2^" << med(rays) << "|map2^" << med(bins);
+    // (k2: choices timed with other kernels, whose entries had no such part, are not used)
+    o << arch << "|k2|lens2^" << med(nl) << "|rays2^" << med(rays) << "|map2^" << med(bins);
     return o.str();
 }
 
