@@ -145,7 +145,9 @@ typedef struct {
 typedef struct {
     int32_t block_cols;      /* rays per lane: block_cols grid columns x block_rows grid rows;  */
     int32_t block_rows;      /* 1x4, 2x2, 2x4, 4x2, 4x4 or 2x8 (0, 0 = default)               */
-    int32_t lens_tile;       /* lenses staged in LDS per tile: 256 or 512 (default 256)        */
+    int32_t lens_tile;       /* lenses staged in LDS per tile: 256 or 512 (default 256); the   */
+                             /* kernels that split a field's lenses over waves stage 64 a wave  */
+                             /* (128 with runs of 32) whatever it is                            */
     int32_t fp32_run;        /* lenses per float32 run: 8, 16 or 32 (default 8 with one column,
                                 16 with several); one-column blocks add four runs in float32
                                 before each FP64 addition, several-column blocks add each run  */

@@ -370,7 +370,7 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
     if (e != hipSuccess) return dev_fail(e, "device query");
     pb.first = std::min<uint32_t>(start[n_split], (uint32_t)taken);
     if (n_split > 0) pb.waves = rs::split_batched_waves(blocks, jobs[order[0]].n_lens);
-    const int split_occ = n_split > 0 ? rs::split_batched_occupancy(t.run(), t.LT, pb.waves) : 1;
+    const int split_occ = n_split > 0 ? rs::split_batched_occupancy(t.run(), pb.waves) : 1;
     const int occ = n_split < n_jobs ? rs::batched_occupancy(t.K1, t.K2, t.run(), t.LT) : 1;
     if (occ <= 0 || split_occ <= 0) return fail(RS_EINTERNAL, "no occupancy for the batched kernel");
 
@@ -408,7 +408,7 @@ int run_batch(const PreparedBatch &pb, const Tune &t, void *workspace, hipStream
         hipError_t e = hipSuccess;
         if (pb.split_grid > 0) {
             e = rs::launch_fill_u32(pb.split.queue, 1, 0u, s);
-            if (e == hipSuccess) e = rs::launch_split_batched(pb.split, t.run(), t.LT, pb.waves, pb.split_grid, s);
+            if (e == hipSuccess) e = rs::launch_split_batched(pb.split, t.run(), pb.waves, pb.split_grid, s);
         }
         if (pb.grid > 0) {
             if (e == hipSuccess) e = rs::launch_fill_u32(pb.args.queue, 1, pb.first, s);
@@ -610,7 +610,7 @@ int shoot_with_partials(const rs_job *job, const Tune &t, uint32_t *part, hipStr
     use_partials(a, part);
     hipError_t e = rs::launch_zero(part, partial_words(job), s);
     if (e != hipSuccess) return dev_fail(e, "zero partial maps");
-    if (t.K1 == 1 && takes_split(job->n_lens, a.n_blocks, t.run())) e = rs::launch_split(a, t.run(), t.LT, s);
+    if (t.K1 == 1 && takes_split(job->n_lens, a.n_blocks, t.run())) e = rs::launch_split(a, t.run(), s);
     else e = rs::launch_direct(a, t.K1, t.K2, t.run(), t.LT, tile_count(job, t), s);
     if (e != hipSuccess) return dev_fail(e, "direct-sum launch");
     e = rs::launch_reduce(part, bins, pstride, job->counts, reinterpret_cast<unsigned long long *>(job->n_lost), s);
@@ -1181,7 +1181,7 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     e = rs::launch_zoom_mark(z, s);
     if (e == hipSuccess && z.flags) e = rs::launch_zoom_rows(cb, z.list, s);
     if (e != hipSuccess) return dev_fail(e, "zoom culling launch");
-    if (split) e = rs::launch_split_cells(a, t.run(), t.LT, cb, s);
+    if (split) e = rs::launch_split_cells(a, t.run(), cb, s);
     else e = rs::launch_direct_cells(a, t.K1, t.K2, t.run(), t.LT, cb, max_groups, s);
     if (e != hipSuccess) return dev_fail(e, "zoom direct-sum launch");
     e = rs::launch_reduce(part, bins, pstride, job->counts, reinterpret_cast<unsigned long long *>(job->n_lost), s);

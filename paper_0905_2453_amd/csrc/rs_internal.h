@@ -262,11 +262,11 @@ bool ray_block_supported(int K1, int K2);
 hipError_t launch_direct(const DirectArgs &a, int K1, int K2, int T, int LT, int64_t n_tiles, hipStream_t s);
 // One-column blocks, lenses split over a workgroup's waves: a window, the lane blocks of a cell list, a batch
 // (WV waves a workgroup, split_batched_waves of the batch's blocks and largest lens count).
-hipError_t launch_split(const DirectArgs &a, int T, int LT, hipStream_t s);
-hipError_t launch_split_cells(const DirectArgs &a, int T, int LT, const CellBlocks &cb, hipStream_t s);
+hipError_t launch_split(const DirectArgs &a, int T, hipStream_t s);
+hipError_t launch_split_cells(const DirectArgs &a, int T, const CellBlocks &cb, hipStream_t s);
 int split_batched_waves(uint64_t blocks, int64_t most_lenses);
-hipError_t launch_split_batched(const BatchArgs &b, int T, int LT, int WV, int grid, hipStream_t s);
-int split_batched_occupancy(int T, int LT, int WV);
+hipError_t launch_split_batched(const BatchArgs &b, int T, int WV, int grid, hipStream_t s);
+int split_batched_occupancy(int T, int WV);
 // Launch the persistent batched kernel on `grid` workgroups.
 hipError_t launch_batched(const BatchArgs &b, int K1, int K2, int T, int LT, int grid, hipStream_t s);
 // Resident workgroups per compute unit of the batched kernel (0 on error).

@@ -482,12 +482,12 @@ int occupancy_batch()
 
 }  // namespace
 
-// Call F<T, B, WV>(args) for the run length, lens tile and waves of a launch.
-#define RS_SPLIT_SWITCH(T, LT, WV, F, ...)                                     \
+// Call F<T, B, WV>(args) for the run length and waves of a launch.  B lenses are staged at a time, 64, or for runs of 32
+// the 128 of a group, then with four waves (300 x 200 rays, 3000 lenses: 66 us, k_direct 267).  Staging 128 with the shorter
+// runs spilled registers and left few blocks fewer waves (the same rays, runs of 8: 72 us, with 64 39).
+#define RS_SPLIT_SWITCH(T, WV, F, ...)                                         \
     do {                                                                       \
         if ((T) == 32) return F<32, 128, 4>(__VA_ARGS__);                      \
-        if ((T) == 16 && (LT) == 512) return F<16, 128, 4>(__VA_ARGS__);       \
-        if ((T) == 8 && (LT) == 512) return F<8, 128, 4>(__VA_ARGS__);         \
         if ((T) == 16 && (WV) == 16) return F<16, 64, 16>(__VA_ARGS__);        \
         if ((T) == 16 && (WV) == 8) return F<16, 64, 8>(__VA_ARGS__);          \
         if ((T) == 16) return F<16, 64, 4>(__VA_ARGS__);                       \
@@ -496,7 +496,7 @@ int occupancy_batch()
         return F<8, 64, 4>(__VA_ARGS__);                                       \
     } while (0)
 
-hipError_t launch_split(const DirectArgs &a, int T, int LT, hipStream_t s)
+hipError_t launch_split(const DirectArgs &a, int T, hipStream_t s)
 {
     if (a.n_blocks == 0) return hipSuccess;
     // Sixteen waves while that gives a compute unit no more than one workgroup (128^2 rays, 12800 lenses:
@@ -505,26 +505,27 @@ hipError_t launch_split(const DirectArgs &a, int T, int LT, hipStream_t s)
     // 21.4 against 20.3) or the field is large (1000^2 rays, 3200 lenses: 427 us against 432, 400 lenses
     // 67.1 against 65.8).
     const int wv = a.n_blocks <= 256 ? 16 : (a.n_lens >= 2048 || (a.n_lens >= 256 && a.n_blocks <= 2048)) ? 8 : 4;
-    RS_SPLIT_SWITCH(T, LT, wv, launch, a, s);
+    RS_SPLIT_SWITCH(T, wv, launch, a, s);
 }
 
-hipError_t launch_split_cells(const DirectArgs &a, int T, int LT, const CellBlocks &cb, hipStream_t s)
+hipError_t launch_split_cells(const DirectArgs &a, int T, const CellBlocks &cb, hipStream_t s)
 {
     if (cb.ncx <= 0 || cb.ncy <= 0) return hipSuccess;
     const int wv = a.n_lens >= 2048 ? 8 : 4;
-    RS_SPLIT_SWITCH(T, LT, wv, launch_cells, a, cb, s);
+    RS_SPLIT_SWITCH(T, wv, launch_cells, a, cb, s);
 }
 
-// Four waves a workgroup: eight leave more waves without lenses in a batch's small fields (64 maps of 128^2 to 512^2
-// rays, 125 to 12 500 lenses: 3.26 ms against 3.35), but a batch of few blocks ends sooner with eight (5 such
-// maps alone: 540 us against 635; 17 of them 587 against 574).
+// Four waves a workgroup: eight leave more of them without lenses in fields of few groups (64 maps of 300^2 rays, us with
+// four and eight: 512 lenses 414, 454; 1000 793, 810; 10 000 7113, 7167), but batches of few blocks end sooner with
+// eight (one map of 256^2 rays: 512 lenses 24, 21; 1000 34, 27; 10 000 207, 129; one of 1000^2, 3000 lenses 405, 393).
+// Between, mixed batches gain a little with eight too (24 maps of 93^2 to 372^2 rays, 90 to 9000 lenses: 258, 233).
 int split_batched_waves(uint64_t blocks, int64_t most_lenses) { return blocks < 4096 && most_lenses >= 256 ? 8 : 4; }
 
-hipError_t launch_split_batched(const BatchArgs &b, int T, int LT, int WV, int grid, hipStream_t s)
+hipError_t launch_split_batched(const BatchArgs &b, int T, int WV, int grid, hipStream_t s)
 {
-    RS_SPLIT_SWITCH(T, LT, WV, launch_batch, b, grid, s);
+    RS_SPLIT_SWITCH(T, WV, launch_batch, b, grid, s);
 }
 
-int split_batched_occupancy(int T, int LT, int WV) { RS_SPLIT_SWITCH(T, LT, WV, occupancy_batch); }
+int split_batched_occupancy(int T, int WV) { RS_SPLIT_SWITCH(T, WV, occupancy_batch); }
 
 }  // namespace rs
