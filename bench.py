@@ -73,18 +73,23 @@ def calibrate_copy(mib: int):
     print(json.dumps({"calibrate_copy_mib": mib, "bytes_read_per_copy": n * 4, "bytes_written_per_copy": n * 4}))
 
 
+def record_current(rec: dict) -> bool:
+    """Whether a committed record belongs to the present kernel source and the headers it includes."""
+    import hashlib
+    files = {rec["source"]: rec["source_sha256"], **rec["headers_sha256"]}
+    return all(hashlib.sha256(open(os.path.join(ROOT, f), "rb").read()).hexdigest() == h for f, h in files.items())
+
+
 def measured_traffic(workload_name: str, opts) -> float | None:
     """HBM bytes per direct-sum launch from the committed rocprofv3 counter passes, or None when the
     kernel source or the launch shape differs from the one the counters were taken on."""
-    import hashlib
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path)).get("k_direct")
     if not rec:
         return None
-    src = open(os.path.join(ROOT, rec["source"]), "rb").read()
-    if hashlib.sha256(src).hexdigest() != rec["source_sha256"] or rec["workload"] != workload_name:
+    if not record_current(rec) or rec["workload"] != workload_name:
         return None
     cols, rows = (opts.block_cols or 1), (opts.block_rows or 4)
     if f"{cols}x{rows}" != rec["block"] or (opts.fp32_run or (8 if cols == 1 else 16)) != rec["fp32_run"] \
@@ -113,21 +118,20 @@ def issue_rates(P):
 def mix_ceiling(rates: dict, opts) -> dict | None:
     """Instruction-mix ceiling of the direct sum's lens loop: the loop's instructions per interaction
     (counted in this build's gfx950 assembly, profiles/k_direct_isa_mix.json, valid while its source
-    is unchanged) priced at the probe rates.  A reciprocal costs what it adds to a 13 : 1 mix of
-    v_fmac_f32 and v_rcp_f32 (the lens loop's own proportion), 14 / R_mix - 13 / R_fmac."""
-    import hashlib
+    is unchanged) priced at the probe rates, every class at that of a stream of its own (a reciprocal
+    among 13 other instructions costs more, 14 / R_mix - 13 / R_fmac, but the loop has 25 to one
+    and other waves' work beside it: priced so, it ran above its ceiling)."""
     path = os.path.join(ROOT, "profiles", "k_direct_isa_mix.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    src = open(os.path.join(ROOT, rec["source"]), "rb").read()
     cols, rows = (opts.block_cols or 1), (opts.block_rows or 4)
-    if hashlib.sha256(src).hexdigest() != rec["source_sha256"] or f"{cols}x{rows}" != rec["block"] \
+    if not record_current(rec) or f"{cols}x{rows}" != rec["block"] \
             or (opts.fp32_run or (8 if cols == 1 else 16)) != rec["fp32_run"] \
             or (opts.lens_tile or 256) != rec["lens_tile"]:
         return None
     k = rec["per_interaction"]
-    rcp_cost = 14.0 / rates["mix_13fmac_1rcp"] - 13.0 / rates["fmac_f32"]
+    rcp_cost = 1.0 / rates["rcp_f32"]
     t = (k["vop2_f32"] / rates["fmac_f32"] + k["vop3_f32"] / rates["fma_f32"] + k["rcp_f32"] * rcp_cost
          + (k["cvt_f64"] + k["add_f64"]) / rates["add_f64"])
     return {"interactions_per_s": 1.0 / t, "tflops_10flop": FLOP_PER_INTERACTION / t / 1e12,

@@ -43,6 +43,12 @@ def _asm(path: str) -> str:
     return open(out).read()
 
 
+def headers_sha256() -> dict:
+    """Hashes of the headers that the direct-sum kernels include."""
+    return {os.path.relpath(p, B.ROOT): hashlib.sha256(open(p, "rb").read()).hexdigest()
+            for p in (os.path.join(B.CSRC, h) for h in ("direct_common.h", "launch_grid.h", "rs_internal.h"))}
+
+
 def _record(src, sym, kernel, block, T, LT, rays_per_rcp, command) -> dict:
     path = os.path.join(B.CSRC, src)
     lines = _asm(path).split("\n")
@@ -74,7 +80,8 @@ def _record(src, sym, kernel, block, T, LT, rays_per_rcp, command) -> dict:
     return {"kernel": kernel, "block": f"{block[0]}x{block[1]}", "fp32_run": T, "lens_tile": LT, "loop_block": name,
             "interactions_per_loop": inter, "per_interaction": per, "loop_histogram": dict(hist.most_common()),
             "source": os.path.relpath(path, B.ROOT),
-            "source_sha256": hashlib.sha256(open(path, "rb").read()).hexdigest(), "command": command}
+            "source_sha256": hashlib.sha256(open(path, "rb").read()).hexdigest(),
+            "headers_sha256": headers_sha256(), "command": command}
 
 
 def count(block=(1, 4), T=0, LT=256) -> dict:
