@@ -1404,7 +1404,6 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
     for (int ps = (int)split; ps < passes; ps += splits) {
         const int qi = 256 * ps + 64 * wave + lane;
         const int ix = qi % n[0], iy = qi / n[0] * ROWS;
-        const int rows = qi < blocks ? min(ROWS, n[1] - iy) : 0;   // the lane's rays
         const int64_t g1 = i0[0] + ix;
         float x1[NX], x2[ROWS];
 #pragma unroll
@@ -1415,7 +1414,9 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
         }
         // far field: network, 32 rays of a row at a time; the outputs come in the half-0 lanes
         float2 (*net)[64] = s_net[wave];
-        if (!f.affine_only) {
+        // (tiles that take four rows fill most of their places: looking for empty ones there spilled registers)
+        const unsigned long long here = ROWS == 1 ? __ballot(qi < blocks) : ~0ull;
+        if (here && !f.affine_only) {
             float u1 = 0.f;
 #pragma unroll
             for (int e = 0; e < ROWS; ++e) {
@@ -1429,7 +1430,7 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
             __builtin_amdgcn_s_setprio(1);
 #pragma unroll 1
             for (int k = 0; k < 2 * ROWS; ++k) {
-                if (!(uint32_t)(__ballot((k >> 1) < rows) >> (32 * (k & 1)))) continue;   // none of the 32 is a ray
+                if (ROWS == 1 && !(uint32_t)(here >> (32 * k))) continue;   // no ray among the 32
                 float2 *ray = &net[k >> 1][32 * (k & 1) + col];
                 const float2 u = *ray;
                 uint32_t phi4[4];
@@ -1444,14 +1445,13 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
         }
         // near field
         double A1[ROWS] = {}, A2[ROWS] = {};
-        const bool any = __any(rows > 0);
         for (int b = 0; b < n_batches; ++b) {
             if (n_batches > 1) {
                 __syncthreads();
                 stage(b);
                 __syncthreads();
             }
-            const int runs = any ? (min(CAP, n_cand - b * CAP) + T - 1) / T : 0;
+            const int runs = here ? (min(CAP, n_cand - b * CAP) + T - 1) / T : 0;
             int at = 0;
             for (int r = 0; r < runs; ++r) {
                 const int end = __builtin_amdgcn_readfirstlane((int)s_near.start[r + 1]);
@@ -1500,7 +1500,7 @@ __global__ void __launch_bounds__(256, 4) k_surrogate(const FarArgs f, const Cel
             const double y1 = f.lam1 * X1 - (F1 + A1[e] * kRcpBiasComp);
             const double y2 = f.lam2 * X2 - (F2 + A2[e] * kRcpBiasComp);
             int key = -2;
-            if (e < rows) {
+            if (qi < blocks && iy + e < n[1]) {
                 const double p1 = floor((y1 - f.mlo1) * f.ms1), p2 = floor((y2 - f.mlo2) * f.ms2);
                 key = (p1 >= 0.0 && p1 < (double)f.mn1 && p2 >= 0.0 && p2 < (double)f.mn2) ? (int)p2 * f.mn1 + (int)p1 : -1;
                 if (DUMP) {
@@ -1657,12 +1657,13 @@ hipError_t launch_surrogate_rows(const FarArgs &f, const CellArgs &g, uint32_t g
 template <bool JIT>
 hipError_t launch_surrogate(const FarArgs &f, const CellArgs &g, uint32_t grid, hipStream_t s)
 {
-    // Four rays a lane share their lens and network reads, but need tiles that fill a pass (at least half as many rays in
-    // it as in passes of one ray a lane) and passes enough for the GPU.  us of an evaluation with four rays and with
-    // one: 1500 x 700 rays in tiles of 64^2 162, 164; 32^2 163, 178; 64 x 5 209, 212; 16^2 225, 191; 8^2 466, 310; 64 x 1 405, 311;
-    // in 64^2 tiles: 500^2 rays (256 passes) 110, 97; 700^2 (484) 120, 119; 1000^2 (1024) 144, 154; 2000^2 298, 322.
+    // Four rays a lane share their lens and network reads, but need tiles that fill their passes (seven eighths of the
+    // places) and passes enough for the GPU.  us of an evaluation with four rays and with one: 1500 x 700 rays in tiles
+    // of 64^2 161, 164; 32^2 162, 178; 48^2 (three quarters) 175, 173; 1024 x 3 202, 183; 64 x 5 269, 212; 16^2 305, 191;
+    // 8^2 894, 310; 64 x 1 900, 311; in 64^2 tiles: 500^2 rays (256 passes) 110, 97; 700^2 (484) 120, 119; 1000^2 (1024) 144,
+    // 154; 2000^2 298, 322.
     const int64_t four = ((int64_t)f.TX * ((f.TY + 3) / 4) + 255) / 256, one = ((int64_t)f.TX * f.TY + 255) / 256;
-    return one >= 2 * four && grid * four >= 768 ? launch_surrogate_rows<JIT, 4>(f, g, grid, s)
+    return 2 * one >= 7 * four && grid * four >= 768 ? launch_surrogate_rows<JIT, 4>(f, g, grid, s)
                                                  : launch_surrogate_rows<JIT, 1>(f, g, grid, s);
 }
 

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("moving,jitter,tile,rays", [
     (False, None, (64, 64), (1000, 900)),      # 240 tiles: four rays a lane, listed ones one
     (False, 5, (64, 64), (1000, 900)),
-    (False, None, (33, 70), (1990, 901)),      # 793 tiles, 7.5 passes of one ray
+    (False, None, (33, 70), (1990, 901)),      # 793 tiles that do not fill passes of four rays a lane
     (False, 3, (16, 9), (700, 500)),           # one ray a lane in both
     (True, None, (64, 64), (1000, 900)),       # a moving field's affine bases: 8 workgroups a tile
     (True, 4, (100, 100), (310, 205)),         # 24, all that the lenses fill
