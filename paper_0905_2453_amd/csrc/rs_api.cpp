@@ -40,9 +40,10 @@ constexpr double kMaxCoord = 1.0e12;  // far below the position of the zero-mass
 
 // Resolved tuning of one direct-sum launch.  T = 0 selects the float32 run length of the block
 // shape: 8 lenses with one column per lane (four rows share a reciprocal), 16 with several (pairs).  W = -1
-// selects its map window: none with one column (its lane runs already merge most rays of a pixel: 1000^2 rays,
-// 400 lenses 73.7 us, with a 16 x 16 window 75.8, with a 64 x 64 one 80.7; 4096 x 2048 rays, 16 lenses, 20 x 20
-// pixels: 54.9, 59.8, 64.9), 64 x 64 with several.
+// selects its map window: none with one column (lane runs already merge most rays of a pixel: k_direct, 4096 x 2048
+// rays, 16 lenses, 20 x 20 pixels 54.9 us, with a 16 x 16 window 59.8, with a 64 x 64 one 64.9; the split kernels
+// have none), 64 x 64 with several, and in k_batched and k_direct_cells, whose maps have no partial ones (batches) or are
+// small (zooms).
 struct Tune {
     int K1 = 1, K2 = 4, T = 0, LT = 256, W = -1;
     int run() const { return T ? T : (K1 == 1 ? 8 : 16); }
@@ -151,10 +152,13 @@ int64_t block_count(const rs_job *job)
 // holds a single run, which k_direct sums as a whole group (4096 x 2048: 96 lenses 149, 124; 100 154, 156; 128 171, 156;
 // 129 181, 188; 160 209, 188; 257 302, 322; but 1400^2: 96 lenses 45, 43; 100 46, 50; 160 61, 59; and with runs of 16
 // 200 lenses 257, 277).  With runs of 32 k_split spills registers: 2048^2 rays, 3000 lenses 1716, 1622; 1000^2 450, 480.
-bool takes_split(int64_t n_lens, int64_t blocks, int T)
+// Jittered rays have no rows to share: 4096 x 2048: 100 lenses 208, 186; 379 551, 510; 700 949, 916; 1000 1320, 1318; 3000
+// 3858, 3825; 1400^2: 100 lenses 59, 55; 300 120, 120; 1000^2, 100 lenses 35, 36.
+bool takes_split(int64_t n_lens, int64_t blocks, int T, bool jitter)
 {
     const int64_t groups = (n_lens + 4 * T - 1) / (4 * T), tail = n_lens - (groups - 1) * 4 * T;
     if (groups <= 2) return blocks < 2048;
+    if (jitter && (blocks >= 16384 ? n_lens < 1024 : blocks >= 6144 && groups <= 4)) return false;
     if (blocks < 16384) return true;
     return T != 32 && !(T == 8 && groups <= 8 && (groups == 3 || tail > T));
 }
@@ -273,14 +277,15 @@ struct PreparedBatch {
 // rays of k_batched's, which fills the GPU where the latter's tiles are few, but does its fixed part and takes its item
 // (12 ns) four times as often, and adds its counts to the job's one map without an LDS window: fewer lenses on a map
 // of few pixels are bound by additions to a cache line.  us of k_split_batched and k_batched: 8 x 2048^2 rays, 64
-// lenses 535, 429; 100 647, 657; 500 2118, 2228; 2000 7839, 8410; on 4 x 4 pixels, 4 x 2048^2 rays, 512 lenses 1348,
+// lenses 535, 429; 100 647, 657; 500 2118, 2228; 2000 7839, 8410; 8 x 1400^2 jittered rays, 512 lenses 1390, 1311, 1000 lenses
+// 2562, 2534 (4 x 700^2, 512: 199, 231); on 4 x 4 pixels, 4 x 2048^2 rays, 512 lenses 1348,
 // 1140, 1000 lenses 2190, 2196; one map of 1000^2 rays: 100 lenses 74, 52; 256 71, 66; 511 96, 112; of 512^2: 100
 // lenses 35, 34; 300 36, 50; of 256^2: 64 lenses 18, 27.
 bool split_job(const rs_job &j, uint64_t blocks, int T)
 {
-    const bool few_pixels = (int64_t)j.map.n[0] * j.map.n[1] <= 1024;
+    const bool more = (int64_t)j.map.n[0] * j.map.n[1] <= 1024 || (j.grid.jitter && blocks >= 16384);
     if (T == 32 && blocks >= 16384) return false;   // as takes_split
-    return j.n_lens >= (few_pixels ? 1024 : 512) || blocks < 8 * (uint64_t)std::max<int64_t>(64, j.n_lens);
+    return j.n_lens >= (more ? 1024 : 512) || blocks < 8 * (uint64_t)std::max<int64_t>(64, j.n_lens);
 }
 
 // Validate, order by kernel and decreasing work per tile, upload the job table into the workspace and fill
@@ -353,7 +358,7 @@ int prepare_batch(const rs_job *jobs, int32_t n_jobs, void *workspace, size_t ws
             nt = ((int64_t)args[k].n_blocks + q - 1) / q;
             rays_per_item = 256ull * (uint64_t)q;
         } else if (t.K1 == 1) {
-            args[k].window = t.W >= 0 ? t.W : 64;
+            args[k].window = t.W >= 0 ? t.W : 64;   // (see Tune)
         }
         items += (uint64_t)nt;
         start[k + 1] = (uint32_t)items;
@@ -610,7 +615,7 @@ int shoot_with_partials(const rs_job *job, const Tune &t, uint32_t *part, hipStr
     use_partials(a, part);
     hipError_t e = rs::launch_zero(part, partial_words(job), s);
     if (e != hipSuccess) return dev_fail(e, "zero partial maps");
-    if (t.K1 == 1 && takes_split(job->n_lens, a.n_blocks, t.run())) e = rs::launch_split(a, t.run(), s);
+    if (t.K1 == 1 && takes_split(job->n_lens, a.n_blocks, t.run(), a.jitter)) e = rs::launch_split(a, t.run(), s);
     else e = rs::launch_direct(a, t.K1, t.K2, t.run(), t.LT, tile_count(job, t), s);
     if (e != hipSuccess) return dev_fail(e, "direct-sum launch");
     e = rs::launch_reduce(part, bins, pstride, job->counts, reinterpret_cast<unsigned long long *>(job->n_lost), s);
@@ -1117,7 +1122,7 @@ int rs_shoot_zoom(const rs_job *job, const rs_zoom *zoom, void *workspace, size_
     const int64_t pstride = partial_stride(job);
     const int64_t bins = (int64_t)job->map.n[0] * job->map.n[1];
     rs::DirectArgs a = make_args(job, t, part, pstride, opts);
-    if (t.K1 == 1 && !split && t.W < 0) a.window = 64;
+    if (t.K1 == 1 && !split && t.W < 0) a.window = 64;   // (see Tune)
     use_partials(a, part);
 
     rs::ZoomArgs z{};

@@ -503,8 +503,10 @@ hipError_t launch_split(const DirectArgs &a, int T, hipStream_t s)
     // 122 us, with eight waves 151, with four 256; but 512 x 640 rays 610, 560, 610); eight where lenses
     // enough for all of them meet few blocks (512 x 640 rays, 400 lenses: 28.4 us against 29.3, 200 lenses
     // 21.4 against 20.3) or the field is large (1000^2 rays, 3200 lenses: 427 us against 432, 400 lenses
-    // 67.1 against 65.8).
-    const int wv = a.n_blocks <= 256 ? 16 : (a.n_lens >= 2048 || (a.n_lens >= 256 && a.n_blocks <= 2048)) ? 8 : 4;
+    // 67.1 against 65.8; jittered rays, which share no rows, later: 4096 x 2048, 2048 lenses 2675 us, with four
+    // 2653, but 1000^2, 6000 lenses 980, 991).
+    const int64_t large = a.jitter ? 4096 : 2048;
+    const int wv = a.n_blocks <= 256 ? 16 : (a.n_lens >= large || (a.n_lens >= 256 && a.n_blocks <= 2048)) ? 8 : 4;
     RS_SPLIT_SWITCH(T, wv, launch, a, s);
 }
 
