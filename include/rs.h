@@ -140,7 +140,12 @@ typedef struct {
  * (one column: four rows share a reciprocal; several columns: pairs of rows
  * share one and the mass is folded into the shared differences, which rounds
  * differently); lens_tile, map_window and the rows of a several-column block
- * change speed, not values.
+ * change speed, not values.  With one column, kernels differ in the order in which
+ * a ray's FP64 additions meet its groups of four float32 runs; the additions
+ * are exact, and the order does not show, while the groups' sums stay within
+ * 2^29 of each other (24-bit numbers in a 53-bit sum).  A ray whose nearest lens
+ * deflects it 2^29 times as far as a group of others may differ in its last bits.
+ * "Bit-identical" and "bit for bit" below hold in this sense.
  */
 typedef struct {
     int32_t block_cols;      /* rays per lane: block_cols grid columns x block_rows grid rows;  */
@@ -220,8 +225,9 @@ size_t rs_batched_workspace_bytes(const rs_job *jobs, int32_t n_jobs);
 
 /*
  * Shoot every job of the host array jobs[0 .. n_jobs) and add each job's counts to its own map.
- * Ray tiles of all jobs form one queue taken by a persistent kernel, costliest jobs first.  On a
- * non-NULL stream the two kernels (counter reset, persistent kernel) are captured once into a
+ * Ray tiles of all jobs form a queue taken by a persistent kernel, costliest jobs first; 1x4 jobs of
+ * few lenses form a second one, taken by another kernel.  On a non-NULL stream the kernels
+ * (counter resets, persistent kernels) are captured once into a
  * HIP graph per (workspace address, block shape, grid, batch size) and replayed on later calls;
  * the job table is uploaded into the workspace before each launch, so later calls may change
  * the jobs' parameters and buffers.  opts: block shape, lens_tile, fp32_run, map_window and
@@ -394,7 +400,8 @@ typedef struct {
     double size;                /* sigma (Gaussian) or radius (disc), source-plane units, > 0  */
     double cutoff;              /* Gaussian support in sigmas (0 = 4); ignored for a disc      */
     int32_t layout;             /* evaluation layout: 0 = chosen by size, 1 = one lane per     */
-                                /* point, 2 = one wave per point (results agree to rounding)   */
+                                /* point, 2 = one wave or workgroup per point (results agree   */
+                                /* to rounding)                                                */
 } rs_source;
 
 /*

@@ -23,7 +23,7 @@ typedef enum {
     RS_PROBE_FMA_F32 = 1,    /* v_fma_f32 (VOP3)                                             */
     RS_PROBE_MUL_F32 = 2,    /* v_mul_f32 (VOP2)                                             */
     RS_PROBE_RCP_F32 = 3,    /* v_rcp_f32 (transcendental unit)                              */
-    RS_PROBE_MIX_13_1 = 4,   /* 13 v_fmac_f32 then 1 v_rcp_f32: the direct sum's per-pair mix */
+    RS_PROBE_MIX_13_1 = 4,   /* 13 v_fmac_f32 then 1 v_rcp_f32: a loop with one per row pair  */
     RS_PROBE_ADD_F64 = 5     /* v_add_f64 (the FP64 run combination)                          */
 } rs_probe_op;
 
