@@ -300,8 +300,8 @@ __device__ __forceinline__ void forward32(const uint16_t *Wbf, const float *sbia
 // alpha_far(c) and its Jacobian over the far set of each tile, FP64; a workgroup takes NT
 // consecutive tiles (of the tile list when one is given), so every lens record it loads serves
 // all of them (NT = 4 when there are enough tiles to fill the GPU, else 1).  Unless SPLIT, each tile's sums are those
-// of a workgroup of its own: thread t takes lenses t, t + 256, ... in order, then a fixed tree adds the 256 partial sums.  At fit
-// time the result goes into the model's tile header.  For a moving field (eval with
+// of a workgroup of its own: thread t takes lenses t, t + 256, ... in order, then a fixed tree adds the 256 partial
+// sums.  At fit time the result goes into the model's tile header.  For a moving field (eval with
 // velocities) the far set is still the one chosen by the fit-time positions, each far lens
 // enters at its position at f.time, and the result goes to f.affine (only the evaluated tiles).
 // SPLIT (moving field, few tiles): S = gridDim.y workgroups share a tile, workgroup y taking lenses

@@ -277,10 +277,10 @@ struct PreparedBatch {
 // rays of k_batched's, which fills the GPU where the latter's tiles are few, but does its fixed part and takes its item
 // (12 ns) four times as often, and adds its counts to the job's one map without an LDS window: fewer lenses on a map
 // of few pixels are bound by additions to a cache line.  us of k_split_batched and k_batched: 8 x 2048^2 rays, 64
-// lenses 535, 429; 100 647, 657; 500 2118, 2228; 2000 7839, 8410; 8 x 1400^2 jittered rays, 512 lenses 1390, 1311, 1000 lenses
-// 2562, 2534 (4 x 700^2, 512: 199, 231); on 4 x 4 pixels, 4 x 2048^2 rays, 512 lenses 1348,
-// 1140, 1000 lenses 2190, 2196; one map of 1000^2 rays: 100 lenses 74, 52; 256 71, 66; 511 96, 112; of 512^2: 100
-// lenses 35, 34; 300 36, 50; of 256^2: 64 lenses 18, 27.
+// lenses 535, 429; 100 647, 657; 500 2118, 2228; 2000 7839, 8410; 8 x 1400^2 jittered rays, 512 lenses 1390, 1311,
+// 1000 lenses 2562, 2534 (4 x 700^2, 512: 199, 231); on 4 x 4 pixels, 4 x 2048^2 rays, 512 lenses 1348, 1140, 1000
+// lenses 2190, 2196; one map of 1000^2 rays: 100 lenses 74, 52; 256 71, 66; 511 96, 112; of 512^2: 100 lenses 35, 34;
+// 300 36, 50; of 256^2: 64 lenses 18, 27.
 bool split_job(const rs_job &j, uint64_t blocks, int T)
 {
     const bool more = (int64_t)j.map.n[0] * j.map.n[1] <= 1024 || (j.grid.jitter && blocks >= 16384);
